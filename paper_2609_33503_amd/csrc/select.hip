@@ -34,12 +34,6 @@ __global__ void clear_error_word(int32_t* counts, int L) {
     if (threadIdx.x == 0 && blockIdx.x == 0) counts[L + 1] = 0;
 }
 
-// A lane's count of set bits of `m` below it (wave64).
-__device__ __forceinline__ int lanes_below(uint64_t m) {
-    return (int)__builtin_amdgcn_mbcnt_hi((uint32_t)(m >> 32),
-                                          __builtin_amdgcn_mbcnt_lo((uint32_t)m, 0u));
-}
-
 // Rows of up to E * 1024 entries: every key is read once and kept in registers.
 // Wave w owns the n_e * 64 consecutive positions from w * n_e * 64 (n_e =
 // ceil(T / 1024) <= E), lane by lane, so loads are coalesced and the compaction

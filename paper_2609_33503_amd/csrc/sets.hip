@@ -4,16 +4,25 @@
 // (rank within R_l, or -1 for a cached row), the CSR lists of R_l and the
 // edge counts sum_{p in R_l} |C_l(p)| and sum_{p in R_l} (p + 1).
 //
-// Four launches: reset h; integer atomicMax of each anchor's layer into h;
-// one workgroup that compacts U in position order and counts |R_l| from the
-// histogram of h; one workgroup per layer that compacts R_l out of U.  All
-// compactions are block prefix scans, so every output is deterministic.
+// Two launches.  The positions are cut into blocks (256 to 16384 positions, at
+// most 256 blocks).  sets_blocks, one workgroup per block, finds each layer's
+// anchors inside its block by search (anchor rows ascend), takes the maximum
+// layer per position in LDS and counts |R_l| within the block.  sets_emit, one
+// wave per (block, layer), adds up the counts of the blocks and layers before it
+// and writes its part of every list, ranking positions by ballots.  Every output
+// is a count or a prefix count of integers, so all are deterministic.
+//
+// Why this split: the lists are a few MB and the work per entry is a handful of
+// instructions, so the time is the length of the dependent chain.  One workgroup
+// for U and one per layer for R_l (with h reset and marked by two launches more)
+// walked the positions in 8192-entry turns: 54 us at 40 layers of 16384 positions
+// and 96 us at 32768, against 16.6 and 19.2 us for these two.
 //
 // Matched-target variants (RelaxKV^G, Sec. 4.1 / App. A.3; the global target
-// sweep of App. B): U is built the same way from the anchors, then every layer
-// takes the same caller-given target list P.  A prefix maximum of the compact
-// map gives each target its compact limit |U cap {j <= p}| - 1 without any
-// search; targets need not lie in U.
+// sweep of App. B): U comes from the anchors the same way, then every layer
+// takes the same caller-given target list P.  The first launch leaves each
+// position's count of union positions within its block, which gives every
+// target its compact limit |U cap {j <= p}| - 1; targets need not lie in U.
 //
 // Context-construction variants (Sec. 4.4): the same anchors and targets R_l;
 // the context list of a layer is replaced by a top-|U| list (of the layer-mean
@@ -27,276 +36,386 @@ namespace relaxkv {
 namespace {
 
 constexpr int kSetThreads = 1024;
-constexpr int kSetPerThread = 8;
+constexpr int kEmitThreads = 256;              // one wave per layer
+constexpr int kEmitWaves = kEmitThreads / 64;
 
-__global__ void sets_reset(int32_t* __restrict__ h, int T, int32_t* __restrict__ rank, long n_rank,
-                           uint32_t* __restrict__ tiles, int n_tiles) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < T; i += gridDim.x * blockDim.x)
-        h[i] = -1;
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n_tiles; i += gridDim.x * blockDim.x)
-        tiles[i] = 0u;
-    for (long i = blockIdx.x * (long)blockDim.x + threadIdx.x; i < n_rank;
-         i += (long)gridDim.x * blockDim.x)
-        rank[i] = -1;
+// Positions per block: the smallest power of two from 256 that needs at most 64
+// blocks (the prefix over blocks is then one load per lane), up to 16384 (its h
+// fits 64 KB of LDS), which at T_c = 2^22 makes 256 blocks.
+int set_block_positions(int T) {
+    int pb = 256;
+    while (pb < 16384 && (T + pb - 1) / pb > 64) pb *= 2;
+    return pb;
 }
 
-__global__ void sets_mark(const int32_t* __restrict__ anchors, int L, int k, int T,
-                          int32_t* __restrict__ h) {
-    const long n = (long)L * k;
-    for (long j = blockIdx.x * (long)blockDim.x + threadIdx.x; j < n;
-         j += (long)gridDim.x * blockDim.x) {
-        const int pos = anchors[j];
-        if (pos >= 0 && pos < T) atomicMax(&h[pos], (int)(j / k));
-    }
-}
-
-// Single workgroup: U, cidx, |U|, |R_l| and R_off.
-__global__ __launch_bounds__(kSetThreads) void sets_union(const int32_t* __restrict__ h, int T,
-                                                          int L, int32_t* __restrict__ U,
-                                                          int32_t* __restrict__ cidx,
-                                                          int32_t* __restrict__ R_off,
-                                                          int32_t* __restrict__ counts) {
-    __shared__ int hist[RELAXKV_MAX_LAYERS];
-    __shared__ int scan_scratch[kSetThreads / 64];
-    const int tid = threadIdx.x;
-    for (int l = tid; l < L; l += kSetThreads) hist[l] = 0;
-    __syncthreads();
-
-    int c_base = 0;
-    for (int base = 0; base < T; base += kSetThreads * kSetPerThread) {
-        const int i0 = base + tid * kSetPerThread;
-        int hv[kSetPerThread];
-        int n = 0;
-#pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e) {
-            const int i = i0 + e;
-            hv[e] = i < T ? h[i] : -1;
-            n += hv[e] >= 0;
+// First index of the ascending list a[0..n) whose entry is >= v, searched by
+// groups of 16 lanes (16 probes a round, so 3 rounds for 4913 entries); every
+// lane of the wave calls, the lanes of a group with the same arguments.  For a
+// list that does not ascend the result is some index in [0, n].
+__device__ __forceinline__ int lower_bound16(const int32_t* __restrict__ a, int n, int v) {
+    const int j = threadIdx.x & 15, shift = threadIdx.x & 48;
+    int lo = 0, hi = n;
+    while (__any(lo < hi)) {
+        const bool open = lo < hi;
+        const int m = hi - lo;
+        const int p = lo + (j + 1) * m / 17;             // < hi for an open interval
+        const bool less = open && a[open ? p : 0] < v;
+        const int c = __popc((uint32_t)(__ballot(less) >> shift) & 0xffffu);
+        if (open) {
+            const int base = lo;
+            if (c > 0) lo = base + c * m / 17 + 1;
+            if (c < 16) hi = base + (c + 1) * m / 17;
         }
-        int tot;
-        int c = block_exclusive_scan<kSetThreads>(n, scan_scratch, tot) + c_base;
-#pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e) {
-            const int i = i0 + e;
-            if (i >= T) break;
-            if (hv[e] >= 0) {
-                U[c] = i;
-                cidx[i] = c;
-                ++c;
-                atomicAdd(&hist[hv[e]], 1);
-            } else {
-                cidx[i] = -1;
+    }
+    return lo;
+}
+
+// Per-block counts the first launch leaves for the second, in the context lists'
+// array (unused until a construction variant fills it).  Anchor targets: n, e, f
+// of (layer, block) at [l * n_blk + b], with n = |R_l| in the block, e the sum of
+// the targets' 1-based union ranks within the block and f that of their 1-based
+// positions within it (each below 2^27).  Global targets: last[i], the number of
+// union positions of i's block up to i, minus one, and n, e, f of the block's
+// targets.  e and f are kept only for more than one block (then 3 L n_blk <= L T,
+// and 2 T + 12 n_blk <= 4 T bytes); a single block writes its sums itself.
+struct BlockScratch {
+    int32_t* n;
+    int32_t* e;
+    int32_t* f;
+    int16_t* last;
+};
+
+// One workgroup per block of positions: h of the block and the counts above (GT:
+// of the targets P instead of R_l; h is written by the second launch).  Also
+// zeroes the attention's work counters.
+template <bool GT>
+__global__ __launch_bounds__(kSetThreads) void sets_blocks(
+    const int32_t* __restrict__ anchors, int L, int k, int T, int pb,
+    const int32_t* __restrict__ P, const int32_t* __restrict__ n_P, int32_t* __restrict__ h,
+    BlockScratch sc, uint32_t* __restrict__ tiles, int n_tiles) {
+    extern __shared__ int hl[];                          // [pb]
+    __shared__ int seg_lo[RELAXKV_MAX_LAYERS], seg_hi[RELAXKV_MAX_LAYERS];
+    __shared__ int wave_n[kSetThreads / 64];
+    __shared__ int sums[3], seg[2];
+    const int b = blockIdx.x, n_blk = gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int b0 = b * pb, len = min(pb, T - b0);
+    for (int i = b * kSetThreads + tid; i < n_tiles; i += n_blk * kSetThreads) tiles[i] = 0u;
+    for (int i = tid; i < pb; i += kSetThreads) hl[i] = -1;
+    for (int l0 = 0; l0 < L; l0 += kSetThreads / 16) {
+        const int l = l0 + tid / 16;
+        const int32_t* row = anchors + (size_t)min(l, L - 1) * k;
+        const int lo = lower_bound16(row, k, b0), hi = lower_bound16(row, k, b0 + len);
+        if (l < L && (tid & 15) == 0) {
+            seg_lo[l] = lo;
+            seg_hi[l] = hi;
+        }
+    }
+    if (GT && w == 0) {                                  // lanes 0-15: b0, the others: b0 + len
+        const int x = lower_bound16(P, min(max(n_P[0], 0), T), lane < 16 ? b0 : b0 + len);
+        if (lane == 0) seg[0] = x;
+        if (lane == 16) seg[1] = x;
+        if (lane < 3) sums[lane] = 0;
+    }
+    __syncthreads();
+    for (int l = w; l < L; l += kSetThreads / 64) {
+        const int32_t* row = anchors + (size_t)l * k;
+        for (int j = seg_lo[l] + lane; j < seg_hi[l]; j += 64) {
+            const int i = row[j] - b0;
+            if (i >= 0 && i < len) atomicMax(&hl[i], l);
+        }
+    }
+    __syncthreads();
+    if constexpr (!GT) {
+        for (int i = tid; i < len; i += kSetThreads) h[b0 + i] = hl[i];
+        for (int l = w; l < L; l += kSetThreads / 64) {
+            int n = 0, u = 0, e = 0, f = 0;
+            for (int c = 0; c < pb; c += 64) {
+                const int hv = hl[c + lane];
+                const uint64_t mu = __ballot(hv >= 0);
+                if (hv >= l) {
+                    e += u + lanes_below(mu) + 1;
+                    f += c + lane + 1;
+                    n += 1;
+                }
+                u += __popcll(mu);
+            }
+            n = wave_sum(n);
+            if (n_blk > 1) {
+                e = wave_sum(e);
+                f = wave_sum(f);
+            }
+            if (lane == 0) {
+                sc.n[(size_t)l * n_blk + b] = n;
+                if (n_blk > 1) {
+                    sc.e[(size_t)l * n_blk + b] = e;
+                    sc.f[(size_t)l * n_blk + b] = f;
+                }
             }
         }
-        c_base += tot;
-    }
-    __syncthreads();
-
-    // |R_l| = #{i : h_i >= l}: suffix sums of the histogram, then R_off is the
-    // exclusive prefix of |R_l| over layers.  L <= 1024 = one layer per thread.
-    const int rl = tid < L ? hist[L - 1 - tid] : 0;
-    int tot1;
-    const int sfx = block_exclusive_scan<kSetThreads>(rl, scan_scratch, tot1) + rl;  // layer L-1-tid
-    __syncthreads();
-    if (tid < L) hist[L - 1 - tid] = sfx;     // hist[l] now holds |R_l|
-    __syncthreads();
-    const int nr = tid < L ? hist[tid] : 0;
-    int tot2;
-    const int off = block_exclusive_scan<kSetThreads>(nr, scan_scratch, tot2);
-    if (tid < L) {
-        R_off[tid] = off;
-        counts[1 + tid] = nr;
-    }
-    if (tid == 0) {
-        R_off[L] = tot2;
-        counts[0] = c_base;
+    } else {
+        const int per = max(64, pb / (kSetThreads / 64));    // positions of a wave
+        const int s0 = w * per;
+        int n = 0;
+        if (s0 < pb)
+            for (int c = s0; c < s0 + per; c += 64) n += __popcll(__ballot(hl[c + lane] >= 0));
+        if (lane == 0) wave_n[w] = n;
+        __syncthreads();
+        int run = 0;
+        for (int ww = 0; ww < w; ++ww) run += wave_n[ww];
+        if (s0 < pb)
+            for (int c = s0; c < s0 + per; c += 64) {
+                const bool in = hl[c + lane] >= 0;
+                const uint64_t m = __ballot(in);
+                const int v = run + lanes_below(m) + in - 1;
+                hl[c + lane] = v;                        // (this lane's own entry)
+                if (c + lane < len) sc.last[b0 + c + lane] = (int16_t)v;
+                run += __popcll(m);
+            }
+        if (n_blk == 1) return;
+        __syncthreads();
+        int tn = 0, te = 0, tf = 0;
+        for (int t = seg[0] + tid; t < seg[1]; t += kSetThreads) {
+            const int i = P[t] - b0;
+            if (i >= 0 && i < len) {
+                tn += 1;
+                te += hl[i] + 1;
+                tf += i + 1;
+            }
+        }
+        tn = wave_sum(tn);
+        te = wave_sum(te);
+        tf = wave_sum(tf);
+        if (lane == 0 && tn) {
+            atomicAdd(&sums[0], tn);
+            atomicAdd(&sums[1], te);
+            atomicAdd(&sums[2], tf);
+        }
+        __syncthreads();
+        if (tid == 0) {
+            sc.n[b] = sums[0];
+            sc.e[b] = sums[1];
+            sc.f[b] = sums[2];
+        }
     }
 }
 
-// One workgroup per layer: R_l in position order, its compact indices, the
-// source map and the edge counts.
-__global__ __launch_bounds__(kSetThreads) void sets_layers(
-    const int32_t* __restrict__ h, const int32_t* __restrict__ U, int T,
-    const int32_t* __restrict__ R_off, const int32_t* __restrict__ counts,
+// The edge counts of a layer from its blocks' n, e, f and the union positions of
+// each block (one wave; u_of(j) is block j's union count): (sum of union ranks,
+// sum of positions), both 1-based, in every lane.
+template <typename UnionOf>
+__device__ __forceinline__ void block_edges(const int32_t* n, const int32_t* e, const int32_t* f,
+                                            int n_blk, int pb, UnionOf u_of, long long& e_sum,
+                                            long long& f_sum) {
+    const int lane = threadIdx.x & 63;
+    long long es = 0, fs = 0;
+    int u0 = 0;                                          // union positions before this turn's blocks
+    for (int j0 = 0; j0 < n_blk; j0 += 64) {
+        const int j = j0 + lane;
+        const int u = j < n_blk ? u_of(j) : 0;
+        const int inc = wave_inclusive_scan(u);
+        if (j < n_blk) {
+            es += e[j] + (long long)(u0 + inc - u) * n[j];
+            fs += f[j] + (long long)j * pb * n[j];
+        }
+        u0 += __shfl(inc, 63, 64);
+    }
+    e_sum = wave_sum(es);
+    f_sum = wave_sum(fs);
+}
+
+// One wave per (block, layer): the block's part of U, cidx (layer 0's wave), R_l,
+// its compact indices, the source map, the rank map and the edge counts.
+__global__ __launch_bounds__(kEmitThreads) void sets_emit(
+    const int32_t* __restrict__ h, int T, int L, int pb, BlockScratch sc,
+    int32_t* __restrict__ U, int32_t* __restrict__ cidx, int32_t* __restrict__ R_off,
     int32_t* __restrict__ R_idx, int32_t* __restrict__ R_u, int32_t* __restrict__ src,
-    int32_t* __restrict__ rank, int64_t* __restrict__ edges, int L) {
-    __shared__ int scan_scratch[kSetThreads / 64];
-    __shared__ long long red[2][kSetThreads / 64];
-    const int l = blockIdx.x;
-    const int tid = threadIdx.x;
-    const int nU = counts[0];
-    const int off = R_off[l];
+    int32_t* __restrict__ rank, int32_t* __restrict__ counts, int64_t* __restrict__ edges) {
+    const int32_t* cnt = sc.n;
+    __shared__ int red[kEmitWaves], tot_sh[kEmitWaves];
+    const int b = blockIdx.x, n_blk = gridDim.x;
+    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int l0 = blockIdx.y * kEmitWaves, l = l0 + w;
+    const int b0 = b * pb;
+    // Entries of the layers before this workgroup's, of this layer (all blocks and
+    // the blocks before this one), and union positions before this block.
+    int before = 0;
+    for (int i = tid; i < l0 * n_blk; i += kEmitThreads) before += cnt[i];
+    int tot = 0, pre = 0, u_base = 0;
+    for (int j = lane; j < n_blk; j += 64) {
+        const int c = l < L ? cnt[(size_t)l * n_blk + j] : 0;
+        tot += c;
+        if (j < b) {
+            pre += c;
+            u_base += cnt[j];
+        }
+    }
+    before = wave_sum(before);
+    tot = wave_sum(tot);
+    pre = wave_sum(pre);
+    u_base = wave_sum(u_base);
+    if (lane == 0) {
+        red[w] = before;
+        tot_sh[w] = tot;
+    }
+    __syncthreads();
+    if (l >= L) return;
+    int off = 0;
+    for (int ww = 0; ww < kEmitWaves; ++ww) off += red[ww];
+    for (int ww = 0; ww < w; ++ww) off += tot_sh[ww];
+    if (b == 0 && lane == 0) {
+        R_off[l] = off;
+        counts[1 + l] = tot;
+        if (l == 0) counts[0] = tot;                     // R_0 = U
+        if (l == L - 1) R_off[L] = off + tot;
+    }
     int32_t* src_l = src + (size_t)l * T;
     int32_t* rank_l = rank + (size_t)l * T;
+    int u = u_base, r = pre;
     long long e_sum = 0, ef_sum = 0;
-    int r_base = 0;
-    for (int base = 0; base < nU; base += kSetThreads * kSetPerThread) {
-        const int c0 = base + tid * kSetPerThread;
-        int pos[kSetPerThread];
-        bool act[kSetPerThread];
-        int n = 0;
+    constexpr int NC = 4;                                // 64-position chunks loaded at once
+    for (int c = 0; c < pb && b0 + c < T; c += NC * 64) {
+        int hv[NC];
 #pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e) {
-            const int c = c0 + e;
-            pos[e] = c < nU ? U[c] : 0;
-            act[e] = c < nU && h[pos[e]] >= l;
-            n += act[e];
+        for (int x = 0; x < NC; ++x) {
+            const int i = b0 + c + x * 64 + lane;
+            hv[x] = i < T ? h[i] : -1;
         }
-        int tot;
-        int r = block_exclusive_scan<kSetThreads>(n, scan_scratch, tot) + r_base;
 #pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e) {
-            const int c = c0 + e;
-            if (c >= nU) break;
-            if (act[e]) {
-                R_idx[off + r] = pos[e];
-                R_u[off + r] = c;
-                src_l[c] = r;
-                rank_l[pos[e]] = r;
-                ++r;
-                e_sum += c + 1;          // |C_l(p)| = compact index of p + 1
-                ef_sum += pos[e] + 1;    // full causal prefix
-            } else {
-                src_l[c] = -1;
+        for (int x = 0; x < NC; ++x) {
+            const int i = b0 + c + x * 64 + lane;
+            const bool in = hv[x] >= 0, act = hv[x] >= l;    // (l >= 0, so act implies in)
+            const uint64_t mu = __ballot(in), ma = __ballot(act);
+            const int uc = u + lanes_below(mu), rc = r + lanes_below(ma);
+            if (i < T) rank_l[i] = act ? rc : -1;
+            if (in) src_l[uc] = act ? rc : -1;
+            if (act) {
+                R_idx[off + rc] = i;
+                R_u[off + rc] = uc;
+                e_sum += uc + 1;                         // |C_l(p)| = compact index of p + 1
+                ef_sum += i + 1;                         // full causal prefix
             }
+            if (l == 0 && i < T) {
+                cidx[i] = in ? uc : -1;
+                if (in) U[uc] = i;
+            }
+            u += __popcll(mu);
+            r += __popcll(ma);
         }
-        r_base += tot;
     }
-    e_sum = wave_sum(e_sum);
-    ef_sum = wave_sum(ef_sum);
-    const int lane = tid & 63, w = tid >> 6;
+    if (b > 0) return;
+    if (n_blk > 1) {
+        const size_t at = (size_t)l * n_blk;
+        block_edges(cnt + at, sc.e + at, sc.f + at, n_blk, pb, [&](int j) { return cnt[j]; }, e_sum, ef_sum);
+    } else {
+        e_sum = wave_sum(e_sum);
+        ef_sum = wave_sum(ef_sum);
+    }
     if (lane == 0) {
-        red[0][w] = e_sum;
-        red[1][w] = ef_sum;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        long long a = 0, b = 0;
-        for (int i = 0; i < kSetThreads / 64; ++i) {
-            a += red[0][i];
-            b += red[1][i];
-        }
-        edges[l] = a;
-        edges[L + l] = b;
+        edges[l] = e_sum;
+        edges[L + l] = ef_sum;
     }
 }
 
 // ------------------------------------------------------ global target lists
 
-__device__ __forceinline__ int wave_inclusive_max(int x) {
-    const int lane = threadIdx.x & 63;
-#pragma unroll
-    for (int o = 1; o < 64; o <<= 1) {
-        const int y = __shfl_up(x, o, 64);
-        if (lane >= o) x = max(x, y);
-    }
-    return x;
-}
-
-// Single workgroup.  last[i] = max_{j <= i} cidx[j] = |U cap {j <= i}| - 1
-// (written into h, which the last launch overwrites); checks the target list;
-// |R_l| = |P| and R_off for every layer.
-__global__ __launch_bounds__(kSetThreads) void gt_prefix(const int32_t* __restrict__ cidx, int T,
-                                                         int L, const int32_t* __restrict__ P,
-                                                         const int32_t* __restrict__ n_P,
-                                                         int32_t* __restrict__ last,
-                                                         int32_t* __restrict__ R_off,
-                                                         int32_t* __restrict__ counts) {
-    __shared__ int wmax[kSetThreads / 64];
-    __shared__ int bad_sh;
+// One wave per (block, layer), every layer with the same targets R_l = P: the
+// block's part of the rank and source maps (layer 0's wave: also U, cidx and h =
+// L - 1 for targets), and the block's share of the target list: positions, compact
+// limits and edge counts.  The first layer group's waves check the list.
+__global__ __launch_bounds__(kEmitThreads) void sets_emit_global(
+    BlockScratch sc, int T, int L, int pb, const int32_t* __restrict__ P,
+    const int32_t* __restrict__ n_P, int32_t* __restrict__ h, int32_t* __restrict__ U,
+    int32_t* __restrict__ cidx, int32_t* __restrict__ R_off, int32_t* __restrict__ R_idx,
+    int32_t* __restrict__ R_u, int32_t* __restrict__ src, int32_t* __restrict__ rank,
+    int32_t* __restrict__ counts, int64_t* __restrict__ edges) {
+    extern __shared__ int trank[];                       // [pb] rank of each position in P
+    const int16_t* last_loc = sc.last;
+    __shared__ int u_base[kEmitThreads];                 // union positions before each block
+    __shared__ int scan_scratch[kEmitWaves];
+    __shared__ int seg[2];
+    const int b = blockIdx.x, n_blk = gridDim.x;         // n_blk <= kEmitThreads
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-    if (tid == 0) bad_sh = 0;
-    int carry = -1;
-    for (int base = 0; base < T; base += kSetThreads * kSetPerThread) {
-        const int i0 = base + tid * kSetPerThread;
-        int v[kSetPerThread];
-        int m = -1;
-#pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e) {
-            v[e] = i0 + e < T ? cidx[i0 + e] : -1;
-            m = max(m, v[e]);
-            v[e] = m;                                  // running max within the thread
-        }
-        const int incl = wave_inclusive_max(m);
-        if (lane == 63) wmax[w] = incl;
-        __syncthreads();
-        int before = carry;                            // max over earlier chunks and waves
-        for (int ww = 0; ww < w; ++ww) before = max(before, wmax[ww]);
-        int prev = __shfl_up(incl, 1, 64);             // earlier lanes of this wave
-        if (lane == 0) prev = -1;
-        const int excl = max(before, prev);
-        int blk = carry;
-        for (int ww = 0; ww < kSetThreads / 64; ++ww) blk = max(blk, wmax[ww]);
-#pragma unroll
-        for (int e = 0; e < kSetPerThread; ++e)
-            if (i0 + e < T) last[i0 + e] = max(excl, v[e]);
-        carry = blk;
-        __syncthreads();
-    }
-    // Target list checks: 0 <= |P| <= T, strictly ascending within [0, T).
+    const int l = blockIdx.y * kEmitWaves + w;
+    const int b0 = b * pb, len = min(pb, T - b0);
     const int n_raw = n_P[0];
     const int n = min(max(n_raw, 0), T);
-    int bad = n_raw < 0 || n_raw > T;
-    for (int t = tid; t < n; t += kSetThreads) {
-        const int p = P[t];
-        bad |= p < 0 || p >= T || (t > 0 && P[t - 1] >= p);
+    const int in_blk = tid < n_blk ? last_loc[min(T, (tid + 1) * pb) - 1] + 1 : 0;
+    for (int i = tid; i < pb; i += kEmitThreads) trank[i] = -1;
+    if (w == 0) {                                        // lanes 0-15: b0, the others: b0 + len
+        const int x = lower_bound16(P, n, lane < 16 ? b0 : b0 + len);
+        if (lane == 0) seg[0] = x;
+        if (lane == 16) seg[1] = x;
     }
-    if (bad) bad_sh = 1;                               // benign race: every writer stores 1
-    for (int l = tid; l <= L; l += kSetThreads) {
-        R_off[l] = l * n;
-        if (l < L) counts[1 + l] = n;
+    int n_u;
+    const int ub = block_exclusive_scan<kEmitThreads>(in_blk, scan_scratch, n_u);
+    u_base[tid] = ub;
+    __syncthreads();
+    for (int t = seg[0] + tid; t < seg[1]; t += kEmitThreads) {
+        const int i = P[t] - b0;
+        if (i >= 0 && i < len) trank[i] = t;
+    }
+    // The block's share of the target list.
+    const int share = (n + n_blk - 1) / n_blk;
+    const int ta = min(n, b * share), tb = min(n, ta + share);
+    if (blockIdx.y == 0) {                               // 0 <= |P| <= T, ascending within [0, T)
+        bool bad = n_raw < 0 || n_raw > T;
+        for (int t = ta + tid; t < tb; t += kEmitThreads) {
+            const int p = P[t];
+            bad |= p < 0 || p >= T || (t > 0 && P[t - 1] >= p);
+        }
+        if (__any(bad) && lane == 0) atomicOr(&counts[L + 1], RELAXKV_ERR_BAD_TARGETS);
+        if (b == 0 && tid == 0) counts[0] = n_u;
     }
     __syncthreads();
-    if (tid == 0 && bad_sh) atomicOr(&counts[L + 1], 2);
-}
-
-// One workgroup per layer: R_l = P, compact limits, the rank and source maps,
-// and the edge counts.
-__global__ __launch_bounds__(kSetThreads) void gt_layers(
-    const int32_t* __restrict__ last, const int32_t* __restrict__ U, int T,
-    const int32_t* __restrict__ P, const int32_t* __restrict__ R_off,
-    const int32_t* __restrict__ counts, int32_t* __restrict__ R_idx, int32_t* __restrict__ R_u,
-    int32_t* __restrict__ src, int32_t* __restrict__ rank, int64_t* __restrict__ edges, int L) {
-    __shared__ long long red[2][kSetThreads / 64];
-    const int l = blockIdx.x, tid = threadIdx.x;
-    const int nU = counts[0], n = counts[1 + l], off = R_off[l];
-    int32_t* src_l = src + (size_t)l * T;
-    int32_t* rank_l = rank + (size_t)l * T;
+    if (l >= L) return;
+    if (b == 0 && lane == 0) {
+        R_off[l] = l * n;
+        counts[1 + l] = n;
+        if (l == L - 1) R_off[L] = L * n;
+    }
     long long e_sum = 0, ef_sum = 0;
-    for (int t = tid; t < n; t += kSetThreads) {
-        const int p = min(max(P[t], 0), T - 1);        // in range even for a rejected list
-        const int u = last[p];
-        R_idx[off + t] = p;
-        R_u[off + t] = u;
-        rank_l[p] = t;
-        e_sum += u + 1;                                // |C_l(p)| = |U cap {j <= p}|
+    for (int t = ta + lane; t < tb; t += 64) {
+        const int p = min(max(P[t], 0), T - 1);          // in range even for a rejected list
+        const int ul = u_base[p / pb] + last_loc[p];     // |U cap {j <= p}| - 1
+        R_idx[l * n + t] = p;
+        R_u[l * n + t] = ul;
+        e_sum += ul + 1;
         ef_sum += p + 1;
     }
-    __syncthreads();                                   // rank_l complete for this layer
-    for (int c = tid; c < nU; c += kSetThreads) src_l[c] = rank_l[U[c]];
-    e_sum = wave_sum(e_sum);
-    ef_sum = wave_sum(ef_sum);
-    const int lane = tid & 63, w = tid >> 6;
-    if (lane == 0) {
-        red[0][w] = e_sum;
-        red[1][w] = ef_sum;
-    }
-    __syncthreads();
-    if (tid == 0) {
-        long long a = 0, b = 0;
-        for (int i = 0; i < kSetThreads / 64; ++i) {
-            a += red[0][i];
-            b += red[1][i];
+    if (b == 0) {
+        if (n_blk > 1) {
+            block_edges(sc.n, sc.e, sc.f, n_blk, pb,
+                        [&](int j) { return last_loc[min(T, (j + 1) * pb) - 1] + 1; }, e_sum, ef_sum);
+        } else {
+            e_sum = wave_sum(e_sum);
+            ef_sum = wave_sum(ef_sum);
         }
-        edges[l] = a;
-        edges[L + l] = b;
+        if (lane == 0) {
+            edges[l] = e_sum;
+            edges[L + l] = ef_sum;
+        }
     }
-}
-
-// h_i = L - 1 for targets, -1 otherwise (after gt_layers read the prefix maxima).
-__global__ void gt_h(const int32_t* __restrict__ rank0, int T, int L, int32_t* __restrict__ h) {
-    for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < T; i += gridDim.x * blockDim.x)
-        h[i] = rank0[i] >= 0 ? L - 1 : -1;
+    int32_t* src_l = src + (size_t)l * T;
+    int32_t* rank_l = rank + (size_t)l * T;
+    int carry = -1;                                      // last_loc before this chunk
+    for (int c = 0; c < len; c += 64) {
+        const int i = c + lane;
+        const int ll = i < len ? last_loc[b0 + i] : 0;
+        int prev = __shfl_up(ll, 1, 64);
+        if (lane == 0) prev = carry;
+        carry = __shfl(ll, 63, 64);                      // (only read again after a full chunk)
+        if (i >= len) continue;
+        const bool in = ll != prev;                      // a union position raises the count
+        const int t = trank[i], uc = u_base[b] + ll;
+        rank_l[b0 + i] = t;
+        if (in) src_l[uc] = t;
+        if (l == 0) {
+            cidx[b0 + i] = in ? uc : -1;
+            if (in) U[uc] = b0 + i;
+            h[b0 + i] = t >= 0 ? L - 1 : -1;
+        }
+    }
 }
 
 // ------------------------------------------------ context-construction variants
@@ -339,18 +458,86 @@ __global__ __launch_bounds__(kSetThreads) void ctx_layers(
     }
 }
 
-void launch_union(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
-    const int T = p.T_c, L = p.L;
-    const long n_rank = (long)L * T;
-    const long rb = (n_rank + 255) / 256;
-    hipLaunchKernelGGL(sets_reset, dim3(rb < 2048 ? (int)rb : 2048), dim3(256), 0, st, s.h, T,
-                       s.rank, n_rank, s.tiles, (int)attn_tile_words(p));
-    const long nm = (long)L * s.k;
-    const long mb = (nm + 255) / 256;
-    hipLaunchKernelGGL(sets_mark, dim3(mb < 2048 ? (int)mb : 2048), dim3(256), 0, st, s.anchors,
-                       L, s.k, T, s.h);
-    hipLaunchKernelGGL(sets_union, dim3(1), dim3(kSetThreads), 0, st, s.h, T, L, s.U, s.cidx,
-                       s.R_off, s.counts);
+// The same with the context list as a bitmap in LDS and a prefix count per
+// 32-position word, so a target's compact limit is two LDS reads instead of a
+// chain of log2 |U| dependent loads.
+__global__ __launch_bounds__(kSetThreads) void ctx_layers_bits(
+    const int32_t* __restrict__ ctx, int ctx_stride, int T, const int32_t* __restrict__ R_off,
+    const int32_t* __restrict__ R_idx, const int32_t* __restrict__ counts,
+    const int32_t* __restrict__ rank, int32_t* __restrict__ R_u, int32_t* __restrict__ src,
+    int64_t* __restrict__ edges) {
+    extern __shared__ uint32_t bits[];                   // [words] membership, [words] prefix counts
+    __shared__ int scan_scratch[kSetThreads / 64];
+    __shared__ long long red[kSetThreads / 64];
+    const int l = blockIdx.x, tid = threadIdx.x;
+    const int words = (T + 31) / 32;
+    uint32_t* pre = bits + words;
+    const int32_t* ctx_l = ctx + (size_t)l * ctx_stride;
+    const int n = counts[0];                             // every context list has |U| entries
+    const int off = R_off[l], nR = counts[1 + l];
+    const int32_t* rank_l = rank + (size_t)l * T;
+    int32_t* src_l = src + (size_t)l * T;
+    for (int i = tid; i < words; i += kSetThreads) bits[i] = 0u;
+    __syncthreads();
+#pragma unroll 4
+    for (int c = tid; c < n; c += kSetThreads) {
+        const int p = ctx_l[c];
+        atomicOr(&bits[p >> 5], 1u << (p & 31));
+        src_l[c] = rank_l[p];
+    }
+    __syncthreads();
+    const int per = (words + kSetThreads - 1) / kSetThreads;
+    const int w0 = min(words, tid * per), w1 = min(words, w0 + per);
+    int sum = 0;
+    for (int i = w0; i < w1; ++i) sum += __popc(bits[i]);
+    int tot;
+    int run = block_exclusive_scan<kSetThreads>(sum, scan_scratch, tot);
+    for (int i = w0; i < w1; ++i) {
+        pre[i] = (uint32_t)run;
+        run += __popc(bits[i]);
+    }
+    __syncthreads();
+    long long e_sum = 0;
+#pragma unroll 4
+    for (int t = tid; t < nR; t += kSetThreads) {
+        const int p = R_idx[off + t];
+        const int m = (int)pre[p >> 5] + __popc(bits[p >> 5] & (0xffffffffu >> (31 - (p & 31))));
+        R_u[off + t] = m - 1;
+        e_sum += m;                                      // |U_l cap {j <= p}|
+    }
+    e_sum = wave_sum(e_sum);
+    if ((tid & 63) == 0) red[tid >> 6] = e_sum;
+    __syncthreads();
+    if (tid == 0) {
+        long long a = 0;
+        for (int i = 0; i < kSetThreads / 64; ++i) a += red[i];
+        edges[l] = a;
+    }
+}
+
+constexpr int kCtxBitsMaxT = 1 << 18;                    // 64 KB of LDS; longer contexts search
+
+int set_blocks(const relaxkv_problem& p, int pb) { return (p.T_c + pb - 1) / pb; }
+
+template <bool GT>
+BlockScratch block_scratch(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk) {
+    BlockScratch sc;
+    const size_t per = GT ? n_blk : (size_t)p.L * n_blk;
+    // (the 16-bit counts take 2 T bytes, rounded up to whole words)
+    sc.n = s.ctx + (GT && n_blk > 1 ? ((size_t)p.T_c + 1) / 2 : 0);
+    sc.e = sc.n + per;
+    sc.f = sc.e + per;
+    sc.last = (int16_t*)s.ctx;
+    return sc;
+}
+
+template <bool GT>
+void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, const int32_t* P,
+                   const int32_t* n_P, hipStream_t st) {
+    const int n_blk = set_blocks(p, pb);
+    hipLaunchKernelGGL(sets_blocks<GT>, dim3(n_blk), dim3(kSetThreads), pb * sizeof(int), st,
+                       s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, block_scratch<GT>(p, s, n_blk),
+                       s.tiles, (int)attn_tile_words(p));
 }
 
 }  // namespace
@@ -369,31 +556,34 @@ hipError_t launch_build_sets_context(const relaxkv_problem& p, const float* scor
     }
     if (e != hipSuccess) return e;
     const int stride = construction == RELAXKV_CONTEXT_SETS_GLOBAL ? 0 : T;
-    hipLaunchKernelGGL(ctx_layers, dim3(L), dim3(kSetThreads), 0, st, (const int32_t*)s.ctx, stride,
-                       T, s.R_off, s.R_idx, s.counts, s.rank, s.R_u, s.src, s.edges);
+    if (T <= kCtxBitsMaxT)
+        hipLaunchKernelGGL(ctx_layers_bits, dim3(L), dim3(kSetThreads), (size_t)(T + 31) / 32 * 8, st,
+                           (const int32_t*)s.ctx, stride, T, s.R_off, s.R_idx, s.counts, s.rank,
+                           s.R_u, s.src, s.edges);
+    else
+        hipLaunchKernelGGL(ctx_layers, dim3(L), dim3(kSetThreads), 0, st, (const int32_t*)s.ctx,
+                           stride, T, s.R_off, s.R_idx, s.counts, s.rank, s.R_u, s.src, s.edges);
     return hipGetLastError();
 }
 
 hipError_t launch_build_sets_global(const relaxkv_problem& p, const relaxkv_sets& s,
                                     const int32_t* targets, const int32_t* n_targets,
                                     hipStream_t st) {
-    const int T = p.T_c, L = p.L;
-    launch_union(p, s, st);
-    hipLaunchKernelGGL(gt_prefix, dim3(1), dim3(kSetThreads), 0, st, s.cidx, T, L, targets,
-                       n_targets, s.h, s.R_off, s.counts);
-    hipLaunchKernelGGL(gt_layers, dim3(L), dim3(kSetThreads), 0, st, (const int32_t*)s.h, s.U, T,
-                       targets, s.R_off, s.counts, s.R_idx, s.R_u, s.src, s.rank, s.edges, L);
-    const int hb = (T + 255) / 256;
-    hipLaunchKernelGGL(gt_h, dim3(hb < 2048 ? hb : 2048), dim3(256), 0, st, (const int32_t*)s.rank,
-                       T, L, s.h);
+    const int T = p.T_c, L = p.L, pb = set_block_positions(T);
+    launch_blocks<true>(p, s, pb, targets, n_targets, st);
+    hipLaunchKernelGGL(sets_emit_global, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
+                       dim3(kEmitThreads), pb * sizeof(int), st,
+                       block_scratch<true>(p, s, set_blocks(p, pb)), T, L, pb, targets, n_targets,
+                       s.h, s.U, s.cidx, s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
     return hipGetLastError();
 }
 
 hipError_t launch_build_sets(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
-    const int T = p.T_c, L = p.L;
-    launch_union(p, s, st);
-    hipLaunchKernelGGL(sets_layers, dim3(L), dim3(kSetThreads), 0, st, s.h, s.U, T, s.R_off,
-                       s.counts, s.R_idx, s.R_u, s.src, s.rank, s.edges, L);
+    const int T = p.T_c, L = p.L, pb = set_block_positions(T);
+    launch_blocks<false>(p, s, pb, nullptr, nullptr, st);
+    hipLaunchKernelGGL(sets_emit, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
+                       dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb,
+                       block_scratch<false>(p, s, set_blocks(p, pb)), s.U, s.cidx, s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
     return hipGetLastError();
 }
 
