@@ -7,7 +7,8 @@
 //
 // bf16 kernel (bf16 MFMA 32x32x16, fp32 accumulation, flash-style online
 // softmax in the exp2 domain):
-// - a workgroup of NW = 12 waves owns NW*32 consecutive (target, head) rows of
+// - a workgroup of NW = 12 waves owns NW*32 consecutive (target, head) rows (in
+//   launches of few tiles a third of that, its waves split over the keys) of
 //   one KV head g (row t*G + hh: target t, the hh-th of the G query heads that
 //   share g), so every K/V row brought into LDS is used by NW*32 rows; a tile
 //   may begin or end inside a target's group of heads, so no row is idle when
@@ -101,12 +102,25 @@ __device__ __forceinline__ float pair_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// NW waves of 32 rows, 64-key steps, one barrier per step.  The fills of step
-// j+3 and the indices of step j+4 are issued right after the barrier of step j,
-// so every fill has two steps of compute to land.
-template <int D, bool FULL, int NW>
+// NW waves as NW / KG groups of 32 rows times KG key groups.
+// KG = 1 (launches with tiles for every CU): 64-key steps, one barrier per step.
+// The fills of step j+3 and the indices of step j+4 are issued right after the
+// barrier of step j, so every fill has two steps of compute to land.
+// KG = 3 (launches with few tiles): a tile is a third of the rows, so there are
+// three times as many workgroups, and each step brings 96 keys through a 3-deep
+// ring, 32 for each key group; the key groups keep their own running max, sum and
+// output, which are combined through LDS after the last step like key splits.
+// The same fills serve a third of the rows, so a step costs more per row; it pays
+// where CUs would stay idle (see attn_key_groups).
+template <int D, bool FULL, int NW, int KG>
 __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
-    constexpr int TK = 64, NST = 4;
+    static_assert(KG == 1 || KG == 3, "key groups");
+    constexpr int NST = KG == 1 ? 4 : 3;   // ring depth
+    constexpr int TKG = KG == 1 ? 64 : 32; // keys per step of a key group
+    constexpr int NKB = TKG / 32;          // 32-key blocks of it
+    constexpr int TK = KG * TKG;           // keys per step
+    constexpr int RG = NW / KG;            // row groups
+    constexpr int IXP = (TK + 63) / 64;    // index loads per step and list
     constexpr int KS = D / 16;             // k-steps of the QK^T contraction
     constexpr int DB = D / 32;             // 32-wide d blocks of O^T
     constexpr int ROWB = 2 * D;            // tile row bytes
@@ -118,7 +132,8 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     constexpr int NWAIT_TAIL = 2 * (NL / NW);  // fills per step of the least busy wave
     __shared__ __attribute__((aligned(1024))) uint16_t Kt[NST][TK * D];
     __shared__ __attribute__((aligned(1024))) uint16_t Vt[NST][TK * D];
-    __shared__ __attribute__((aligned(256))) int32_t Ix[NST][2][TK];   // [U or rank, src]
+    __shared__ __attribute__((aligned(256))) int32_t Ix[NST][2][IXP * 64];   // [U or rank, src]
+    auto ring = [](int m) { return NST == 4 ? m & 3 : m % NST; };
 
     __shared__ int s_pick;
 
@@ -126,46 +141,64 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int nR_dev = a.counts[1 + a.layer];
     const int nR = min(nR_dev, a.cap);
     if (nR_dev > a.cap && blockIdx.x == 0 && threadIdx.x == 0) atomicOr(a.err, RELAXKV_ERR_ROWS);
-    constexpr int TR = NW * 32;            // (target, head) rows per tile
-    const int nrows = nR * a.G;            // rows of one KV head (< 2^31: T_c <= 2^22, G <= TR)
+    constexpr int TR = RG * 32;            // (target, head) rows per tile
+    const int nrows = nR * a.G;            // rows of one KV head (< 2^31: T_c <= 2^22, G <= kAttnRows)
     const int ntiles = (nrows + TR - 1) / TR;
-    // Tile choice.  Each KV head's tiles are handed out heaviest first from its
+    const int off = a.R_off[a.layer];
+    const int idx_max = max((FULL ? a.T : a.counts[0]) - 1, 0);   // last entry of the context list
+    // Tile choice, KG = 1.  Each KV head's tiles are handed out heaviest first from its
     // counter; a workgroup starts with a head tied to its XCD (so the
     // workgroups of one XCD share that head's K/V in their L2) and moves on to
     // the next head once that one is exhausted.  The XCDs run at different
     // clocks, so a fixed blockIdx -> tile map would make every launch wait for
     // the slowest; the grid carries spare workgroups for the faster ones.  The
-    // last workgroup to take its pick returns the counters to zero for the
-    // next launch of this layer and mode.
-    if (threadIdx.x == 0) {
-        const int xcc = (int)__builtin_amdgcn_s_getreg(kHwRegXccId | ((4 - 1) << 11));
-        int h = (xcc + kXcds * (int)((blockIdx.x / kXcds) % ((Hkv + kXcds - 1) / kXcds))) % Hkv;
-        int pick = -1;
-        for (int tried = 0; tried < Hkv; ++tried) {
-            const int t = (int)atomicAdd(a.tiles + h, 1u);
-            if (t < ntiles) {
-                pick = t * Hkv + h;
-                break;
+    // last workgroup to finish returns the counters to zero for the next launch
+    // of this layer and mode (it is counted after its pick was handed out, which
+    // the pick's returned value proves, so every other pick happened before).
+    // KG = 3: workgroup i takes head i mod Hkv, heaviest tiles first (also one head
+    // per XCD at 8 heads); such a launch is one to three rounds of workgroups, so
+    // the spread of the XCDs' clocks costs less than the counters' round trips.
+    int pick = blockIdx.x;
+    if constexpr (KG == 1) {
+        if (threadIdx.x == 0) {
+            const int xcc = (int)__builtin_amdgcn_s_getreg(kHwRegXccId | ((4 - 1) << 11));
+            int h = (xcc + kXcds * (int)((blockIdx.x / kXcds) % ((Hkv + kXcds - 1) / kXcds))) % Hkv;
+            int got = -1;
+            for (int tried = 0; tried < Hkv; ++tried) {
+                const int t = (int)atomicAdd(a.tiles + h, 1u);
+                if (t < ntiles) {
+                    got = t * Hkv + h;
+                    break;
+                }
+                h = h + 1 == Hkv ? 0 : h + 1;
             }
-            h = h + 1 == Hkv ? 0 : h + 1;
+            s_pick = got;
         }
-        s_pick = pick;
-        __threadfence();
-        if (atomicAdd(a.tiles + Hkv, 1u) == gridDim.x - 1) {
-            __threadfence();                       // every other pick happens before the resets
-            for (int i = 0; i < Hkv; ++i) atomicExch(a.tiles + i, 0u);
-            atomicExch(a.tiles + Hkv, 0u);
-        }
+        __syncthreads();
+        pick = s_pick;
+    } else if (pick >= ntiles * Hkv) {
+        return;
     }
-    __syncthreads();
-    const int pick = s_pick;
-    if (pick < 0) return;
+    // Counts this workgroup as done with the counters; the last one clears them.
+    auto leave = [&] {
+        if (KG == 1 && threadIdx.x == 0) {
+            __threadfence();
+            if (atomicAdd(a.tiles + Hkv, 1u) == gridDim.x - 1) {
+                __threadfence();                   // every other pick happens before the resets
+                for (int i = 0; i < Hkv; ++i) atomicExch(a.tiles + i, 0u);
+                atomicExch(a.tiles + Hkv, 0u);
+            }
+        }
+    };
+    if (pick < 0) {
+        leave();
+        return;
+    }
     const int g = pick % Hkv;
     const int tile = ntiles - 1 - pick / Hkv;        // heaviest tiles first
     const int r0 = tile * TR;                        // the tile's rows [r0, r1)
     const int r1 = min(r0 + TR, nrows);
     const int t0 = r0 / a.G, t1 = (r1 - 1) / a.G + 1;  // the targets they belong to
-    const int off = a.R_off[a.layer];
     const int32_t* lim_of = FULL ? a.R_idx + off : a.R_u + off;
     const int cmin = lim_of[t0];
     const int cmax = max(lim_of[t1 - 1], 0);
@@ -174,8 +207,9 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, hf = lane >> 5;
     const float sl2 = a.scale * kLog2e;
+    const int rg = KG == 1 ? w : w % RG, kg = KG == 1 ? 0 : w / RG;
 
-    const int row = r0 + w * 32 + r32;
+    const int row = r0 + rg * 32 + r32;
     const bool valid = row < r1;
     const int t_row = valid ? row / a.G : t0;
     const int hh = valid ? row - t_row * a.G : 0;
@@ -183,7 +217,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int lim = valid ? lim_v : cmax;
     // The largest limit among the wave's rows (limits ascend with the row), -1
     // for a wave without rows: steps past it are masked for every row of the wave.
-    const int w_first = r0 + w * 32, w_last = min(w_first + 31, r1 - 1);
+    const int w_first = r0 + rg * 32, w_last = min(w_first + 31, r1 - 1);
     const int wlim = __builtin_amdgcn_readfirstlane(w_last < w_first ? -1 : lim_of[w_last / a.G]);
     const int head = g * a.G + hh;
     bf16x8 qf[KS];
@@ -191,15 +225,18 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         const uint16_t* qrow = (const uint16_t*)a.q_new + ((size_t)t_row * a.H + head) * D;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[ks] = *(const bf16x8*)(qrow + ks * 16 + hf * 8);
-        // Consumed here, so the compiler's waits for these loads stay before the
-        // loop: inside it they would also wait for the K/V fills just issued.
+    }
+    // Consumed before the loop, so the compiler's waits for these loads stay
+    // there: inside it they would also wait for the K/V fills just issued.
+    auto use_q = [&] {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) asm volatile("" : "+v"(qf[ks]));
-    }
+    };
+    if (KG == 1) use_q();
     f32x16 o[DB];
 #pragma unroll
     for (int db = 0; db < DB; ++db) o[db] = f32x16{};
-    float m_run = lim < 0 ? 0.f : -INFINITY;       // empty context: every p is exp2(-inf) = 0
+    float m_run = KG == 1 && lim < 0 ? 0.f : -INFINITY;   // empty context: every p is exp2(-inf) = 0
     float l_run = 0.f;
 
     // Row bases of the fresh rows (stride Hkv*D) and of the cached layer (stride D).
@@ -209,15 +246,18 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const uint16_t* vcg = (const uint16_t*)a.vc + g * a.kv_sh;
     const uint32_t kst = (uint32_t)a.kv_st;              // < 2^24 (checked on the host)
     const int32_t* srcmap = FULL ? a.rank_l : a.src_l;
-    const int S = cmax / TK + 1;                     // 64-key steps
+    const int S = cmax / TK + 1;                     // steps
 
     auto issue_idx = [&](int m) {
-        if (w < (FULL ? 1 : 2)) {
-            int ww = w;
+        if (w < (FULL ? 1 : 2) * IXP) {
+            int ww = w / IXP;
             asm volatile("" : "+s"(ww));
-            const int c = min(m * TK + lane, cmax);
+            const int part = IXP == 1 ? 0 : w % IXP * 64;
+            // (KG = 3: clamped to the list, which is known before the tile's limits; the
+            // fills then clamp to cmax)
+            const int c = min(m * TK + part + lane, KG == 1 ? cmax : idx_max);
             const int32_t* src = FULL ? srcmap + c : (ww == 0 ? a.U + c : srcmap + c);
-            fill_lds4(src, lds_addr(&Ix[m & 3][ww][0]));
+            fill_lds4(src, lds_addr(&Ix[ring(m)][ww][part]));
         }
     };
     // The lane's tile row and swizzled chunk offset (elements) in each of its
@@ -230,7 +270,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         f_choff[i] = (uint32_t)(((lane % CH) ^ tile_swz<D>(f_row[i])) << 3);
     }
     auto issue_rows = [&](int m) {
-        const int st = m & 3;
+        const int st = ring(m);
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const int j = w + i * NW;
@@ -238,6 +278,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
                 int row = f_row[i];
                 uint32_t choff = f_choff[i];
                 asm volatile("" : "+v"(row), "+v"(choff));
+                if (KG > 1) row = min(row, cmax - m * TK);
                 const int c = m * TK + row;
                 int pos = FULL ? min(c, cmax) : Ix[st][0][row];
                 int r = Ix[st][FULL ? 0 : 1][row];
@@ -267,8 +308,9 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
 
 #pragma unroll
     for (int m = 0; m < NST; ++m)
-        if (m < S) issue_idx(m);
+        if (KG > 1 || m < S) issue_idx(m);
     wait_loads_barrier<0>();
+    if (KG > 1) use_q();
 #pragma unroll
     for (int m = 0; m < NST - 1; ++m)
         if (m < S) issue_rows(m);
@@ -281,25 +323,29 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         // its loads are outstanding as it issued after them: the fills of steps
         // j+1 and j+2 (at least NWAIT loads while both steps exist), only those
         // of step j+1 near the end (at least NWAIT_TAIL), none in the last step.
-        if (j + 2 < S) wait_loads_barrier<NWAIT>();
+        // (3-deep ring: one step less; only the fills of step j+1 may be in flight.)
+        if (NST == 4 && j + 2 < S) wait_loads_barrier<NWAIT>();
         else if (j + 1 < S) wait_loads_barrier<NWAIT_TAIL>();
         else wait_loads_barrier<0>();
         if (j + NST < S) issue_idx(j + NST);
         if (j + NST - 1 < S) issue_rows(j + NST - 1);
         // A step whose keys all lie past every limit of the wave's rows adds
         // exact zeros to them (p = 0): the wave only keeps the ring moving.
-        if (j * TK > wlim) continue;
-        // S^T = K Q^T: s[kb][v] = S[row][key 64 j + 32 kb + 8(v/4) + 4 hf + v%4]
-        f32x16 s[2];
+        const int c0 = j * TK + kg * TKG;              // the wave's first key of this step
+        if (c0 > wlim) continue;
+        // S^T = K Q^T: s[kb][v] = S[row][key c0 + 32 kb + 8(v/4) + 4 hf + v%4]
+        f32x16 s[NKB];
         {
-            int kbo = k_base + (j & 3) * (TK * D * 2);    // the stage offset leaves the swizzled bits alone
+            // (the stage and key-group offsets leave the swizzled bits alone)
+            int kbo = k_base + ring(j) * (TK * D * 2) + (KG == 1 ? 0 : kg * TKG * ROWB);
             asm volatile("" : "+v"(kbo));
             const char* kst = (const char*)Kt[0];
-            s[0] = s[1] = f32x16{};
-            // K fragments x = 2 ks + kb, read KA ahead of their MFMA.
-            constexpr int KA = RELAXKV_ATTN_KAHEAD < 2 * KS ? RELAXKV_ATTN_KAHEAD : 2 * KS;
+#pragma unroll
+            for (int kb = 0; kb < NKB; ++kb) s[kb] = f32x16{};
+            // K fragments x = NKB ks + kb, read KA ahead of their MFMA.
+            constexpr int KA = RELAXKV_ATTN_KAHEAD < NKB * KS ? RELAXKV_ATTN_KAHEAD : NKB * KS;
             auto frag = [&](int x) {
-                return *(const bf16x8*)(kst + (x & 1) * 32 * ROWB + (kbo ^ ((x >> 1) << 5)));
+                return *(const bf16x8*)(kst + (x % NKB) * 32 * ROWB + (kbo ^ ((x / NKB) << 5)));
             };
             bf16x8 kf[KA];
 #pragma unroll
@@ -308,71 +354,75 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
             __builtin_amdgcn_s_setprio(2);
 #endif
 #pragma unroll
-            for (int x = 0; x < 2 * KS; ++x) {
+            for (int x = 0; x < NKB * KS; ++x) {
                 const bf16x8 cur = kf[x % KA];
-                if (x + KA < 2 * KS) kf[x % KA] = frag(x + KA);
-                s[x & 1] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, qf[x >> 1], s[x & 1], 0, 0, 0);
+                if (x + KA < NKB * KS) kf[x % KA] = frag(x + KA);
+                s[x % NKB] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(cur, qf[x / NKB], s[x % NKB], 0, 0, 0);
             }
 #if RELAXKV_ATTN_SCHED
             __builtin_amdgcn_sched_group_barrier(0x100, KA, 0);
 #pragma unroll
-            for (int x = 0; x < 2 * KS; ++x) {
+            for (int x = 0; x < NKB * KS; ++x) {
                 __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
-                if (x + KA < 2 * KS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+                if (x + KA < NKB * KS) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
             }
 #endif
 #if RELAXKV_ATTN_SETPRIO
             __builtin_amdgcn_s_setprio(0);
 #endif
         }
-        const int c0 = j * TK;
-        if (c0 + TK - 1 > cmin) {                      // staircase step: mask
+        if (c0 + TKG - 1 > cmin) {                     // staircase step: mask
             const int ex = lim - c0 - 4 * hf;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                if (8 * (v >> 2) + (v & 3) > ex) s[0][v] = -INFINITY;
-                if (32 + 8 * (v >> 2) + (v & 3) > ex) s[1][v] = -INFINITY;
+#pragma unroll
+                for (int kb = 0; kb < NKB; ++kb)
+                    if (32 * kb + 8 * (v >> 2) + (v & 3) > ex) s[kb][v] = -INFINITY;
             }
         }
 #if RELAXKV_ATTN_LEAN
         // Two chains of 3-input maxima (two new values per instruction).
-        float m0 = fmaxf(s[0][0], s[0][1]), m1 = fmaxf(s[1][0], s[1][1]);
+        float m0 = fmaxf(s[0][0], s[0][1]), m1 = fmaxf(s[NKB - 1][0], s[NKB - 1][1]);
 #pragma unroll
         for (int v = 2; v < 16; v += 2) {
             m0 = fmaxf(fmaxf(m0, s[0][v]), s[0][v + 1]);
-            m1 = fmaxf(fmaxf(m1, s[1][v]), s[1][v + 1]);
+            if (NKB == 2) m1 = fmaxf(fmaxf(m1, s[NKB - 1][v]), s[NKB - 1][v + 1]);
         }
         const float mx = pair_max(fmaxf(m0, m1)) * sl2;
 #else
-        float m = fmaxf(s[0][0], s[1][0]);
+        float m = fmaxf(s[0][0], s[NKB - 1][0]);
 #pragma unroll
-        for (int v = 1; v < 16; ++v) m = fmaxf(m, fmaxf(s[0][v], s[1][v]));
+        for (int v = 1; v < 16; ++v) m = fmaxf(m, fmaxf(s[0][v], s[NKB - 1][v]));
         const float mx = pair_max(m) * sl2;
 #endif
         const bool need = mx > m_run + kRescaleSlack;
         if (__any(need)) {
             const float m_new = need ? mx : m_run;
-            const float alpha = fast_exp2(m_run - m_new);
+            // (a key group's row may still be at -inf: -inf - -inf is no number)
+            const float alpha = KG > 1 && !need ? 1.f : fast_exp2(m_run - m_new);
             l_run *= alpha;
 #pragma unroll
             for (int db = 0; db < DB; ++db) o[db] *= alpha;
             m_run = m_new;
         }
-        bf16x8 pb[2][2];
+        // (a key group can meet steps whose keys are all masked for a row before the
+        // row's first visible key: its reference is then 0, so they add exact zeros)
+        const float m_ref = KG > 1 && m_run == -INFINITY ? 0.f : m_run;
+        bf16x8 pb[NKB][2];
 #if RELAXKV_ATTN_LEAN
         // The row sum adds the bf16 probabilities that the PV product uses, two
         // per dot2 instruction, in four chains.
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                pb[kb][v >> 3][v & 7] = (__bf16)fast_exp2(fmaf(s[kb][v], sl2, -m_run));
+                pb[kb][v >> 3][v & 7] = (__bf16)fast_exp2(fmaf(s[kb][v], sl2, -m_ref));
         {
             typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
             const bf16x2 one2 = {(__bf16)1.0f, (__bf16)1.0f};
             float ls0 = 0.f, ls1 = 0.f, ls2 = 0.f, ls3 = 0.f;
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int k2 = 0; k2 < 2; ++k2) {
                     const bf16x8 q8 = pb[kb][k2];
@@ -386,10 +436,10 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
 #else
         float ls = 0.f;
 #pragma unroll
-        for (int kb = 0; kb < 2; ++kb)
+        for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
-                const float p = fast_exp2(fmaf(s[kb][v], sl2, -m_run));
+                const float p = fast_exp2(fmaf(s[kb][v], sl2, -m_ref));
                 ls += p;
                 pb[kb][v >> 3][v & 7] = (__bf16)p;
             }
@@ -399,14 +449,15 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         {
             // LDS byte addresses of the lane's two V rows in this step's tile: the
             // tile base and stage only set bits above the swizzled chunk bits.
-            const uint32_t vstage = lds_addr(Vt[0]) + (uint32_t)(j & 3) * (TK * D * 2);
+            const uint32_t vstage = lds_addr(Vt[0]) + (uint32_t)ring(j) * (TK * D * 2) +
+                                    (KG == 1 ? 0u : (uint32_t)(kg * TKG * ROWB));
             uint32_t vb0 = v_base0 + vstage, vb1 = v_base1 + vstage;
             asm volatile("" : "+v"(vb0), "+v"(vb1));
 #if RELAXKV_ATTN_SETPRIO
             __builtin_amdgcn_s_setprio(2);
 #endif
 #pragma unroll
-            for (int kb = 0; kb < 2; ++kb)
+            for (int kb = 0; kb < NKB; ++kb)
 #pragma unroll
                 for (int db = 0; db < DB; ++db)
 #pragma unroll
@@ -426,7 +477,40 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         }
     }
 
-    const float l_tot = pair_sum(l_run);
+    float l_tot = pair_sum(l_run);
+    if constexpr (KG > 1) {
+        // Key groups 1 and 2 hand their (O, m, l) to the row group's first wave
+        // through the ring's LDS (free: the last fills were waited for and read).
+        constexpr int OW = DB * 16 * 64;                   // floats of one wave's O
+        static_assert((RG * (OW + 128)) * 4 <= (int)sizeof(Kt), "one key group's hand-over per tensor");
+        __syncthreads();
+        if (kg > 0) {
+            float* mo = (float*)(kg == 1 ? &Kt[0][0] : &Vt[0][0]) + rg * (OW + 128) + lane;
+#pragma unroll
+            for (int db = 0; db < DB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mo[(db * 16 + v) * 64] = o[db][v];
+            mo[OW] = m_run;
+            mo[OW + 64] = l_tot;
+        }
+        __syncthreads();
+        if (kg > 0) return;
+        const float* p1 = (const float*)&Kt[0][0] + rg * (OW + 128) + lane;
+        const float* p2 = (const float*)&Vt[0][0] + rg * (OW + 128) + lane;
+        const float m1 = p1[OW], m2 = p2[OW];
+        const float m = fmaxf(m_run, fmaxf(m1, m2));
+        const float w0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m);
+        const float w1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - m);
+        const float w2 = m2 == -INFINITY ? 0.f : fast_exp2(m2 - m);
+#pragma unroll
+        for (int db = 0; db < DB; ++db)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                o[db][v] = o[db][v] * w0 + p1[(db * 16 + v) * 64] * w1 + p2[(db * 16 + v) * 64] * w2;
+        l_tot = l_tot * w0 + p1[OW + 64] * w1 + p2[OW + 64] * w2;
+        m_run = m;
+    }
+    leave();
     if (!valid) return;
     const bool empty = lim < 0;
     const float inv = empty ? 0.f : 1.0f / l_tot;
@@ -520,16 +604,34 @@ __global__ __launch_bounds__(64) void attn_f32(AttnArgs a) {
 constexpr int kNW = RELAXKV_ATTN_WAVES;
 static_assert(kAttnRows == kNW * 32, "rows per workgroup");
 
+// Key groups of a launch of `rows` (target, head) rows per KV head: one while
+// whole tiles outnumber the chip's 256 CUs, three otherwise.  Up to there every
+// tile has a CU to itself and the launch lasts as long as the longest tile's
+// steps, so a third of the rows and of the steps per workgroup is shorter; past
+// it the extra fills per row count.  Measured, one against three key groups, d
+// 128, 8 KV heads: 24 tiles (1.5K context) 28.1 / 20.4 us, 104 (8K) 163 / 89,
+// 160 (8K) 165 / 102, 264 (8K) 175 / 169, 264 (16K) 345 / 315, 312 (8K) 185 / 191,
+// 408 (8K) 206 / 249; d 64, 2 KV heads: 140 (5K, full prefix) 117 / 63, 312 (8K, 8
+// KV heads) 125 / 128.
+int attn_key_groups(long rows, int Hkv) {
+    constexpr long kCUs = 256;
+    return (rows + kAttnRows - 1) / kAttnRows * Hkv <= kCUs ? 3 : 1;
+}
+
 template <int D, bool FULL>
 void launch_one(const AttnArgs& a, bool bf16, int n_bound, hipStream_t st) {
     n_bound = n_bound > 0 ? n_bound : 1;                 // workgroup 0 still checks the count
     if (bf16) {
         const long rows = (long)n_bound * a.G;
-        const int ntiles = (int)((rows + kAttnRows - 1) / kAttnRows);
-        const int nwg = ntiles * a.Hkv;
-        // One workgroup per tile of the bound plus an eighth spare (they exit
-        // once every counter is exhausted).
-        hipLaunchKernelGGL((attn_bf16<D, FULL, kNW>), dim3(nwg + nwg / 8), dim3(kNW * 64), 0, st, a);
+        const int kg = attn_key_groups(rows, a.Hkv);
+        const int tr = kAttnRows / kg;                   // rows of a tile
+        const int nwg = (int)((rows + tr - 1) / tr) * a.Hkv;
+        // One workgroup per tile of the bound, plus an eighth spare where they take
+        // their tiles from the counters (they exit once every one is exhausted).
+        if (kg == 1)
+            hipLaunchKernelGGL((attn_bf16<D, FULL, kNW, 1>), dim3(nwg + nwg / 8), dim3(kNW * 64), 0, st, a);
+        else
+            hipLaunchKernelGGL((attn_bf16<D, FULL, kNW, 3>), dim3(nwg), dim3(kNW * 64), 0, st, a);
     } else {
         hipLaunchKernelGGL((attn_f32<D, FULL>), dim3(n_bound, a.H), dim3(64), 0, st, a);
     }

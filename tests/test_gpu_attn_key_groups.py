@@ -1,0 +1,46 @@
+"""The bf16 attention on both sides of its key-group rule: launches of at most 256
+384-row tiles split each workgroup's keys over three wave groups, larger ones do
+not.  Sampled targets (the first ones, whose contexts end inside the first key
+group's keys, and the last of a ragged tile among them) against the oracle, and
+the work counters are zero afterwards on both sides."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from harness import Case, assert_close, synthetic_scores
+from paper_2609_33503_amd import relaxkv, synth
+
+pytestmark = pytest.mark.gpu
+
+W = synth.WORKLOADS["llama8b-8k"]
+
+
+# 32 KV heads: 8 tiles each make 256.  G = 4 at 768 targets fills them exactly.
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,G,n", [(97, 1, 97), (96, 3, 33), (801, 4, 768), (801, 4, 769), (1100, 5, 700)])
+def test_key_groups(gpu_lib, T, G, n, d):
+    w = synth.shrink(W, L=2, T_c=T, H=32 * G, H_kv=32, d=d, Qn=2)
+    case = Case(w, ratio=0.4)
+    a = synthetic_scores(2, T, seed=T)
+    anchors = oracle.select(a.astype(np.float64), case.k)
+    assert np.array_equal(case.gpu_select(torch.from_numpy(a).cuda()), anchors)
+    rng = np.random.default_rng(n + d)
+    P = np.sort(rng.choice(T, size=n, replace=False))      # some with empty contexts
+    t = torch.zeros(T, dtype=torch.int32, device="cuda")
+    t[:n] = torch.from_numpy(P.astype(np.int32)).cuda()
+    case.req.build_sets_global(case.sets, t, torch.tensor([n], dtype=torch.int32, device="cuda"))
+    case.sets.counts_to_host()
+    ref = oracle.build_sets_global(anchors, T, P)
+    ts = sorted(set(list(range(4)) + [n // 2, n - 2, n - 1] + rng.integers(0, n, 6).tolist()))
+    fresh = case.fresh(1, P)
+    for mode, cm in (("union", relaxkv.CONTEXT_UNION), ("full", relaxkv.CONTEXT_FULL)):
+        out, lse = case.gpu_attn(1, fresh, n, cm)
+        O_ref, lse_ref = case.oracle_attn(1, ref, fresh, mode=mode, targets=ts)
+        empty = np.isneginf(lse_ref)
+        got, got_lse = out[ts].float().cpu().numpy(), lse[ts].cpu().numpy()
+        assert np.array_equal(np.isneginf(got_lse), empty) and not got[empty].any()
+        assert_close(got[~empty], O_ref[~empty], w, f"{mode} out", rel_gate=1e-2)
+        assert_close(got_lse[~empty], lse_ref[~empty], w, f"{mode} lse")
+        assert int(case.sets.tiles.abs().sum()) == 0
