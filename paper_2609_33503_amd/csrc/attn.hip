@@ -31,12 +31,12 @@
 //   to its XCD, so the workgroups of one XCD share a KV head and its L2
 //   working set, and takes the next head's tiles once its own are gone (the
 //   XCDs run at different clocks, and a fixed map would wait for the slowest).
-// fp32 kernel: one wave per (target, head), VALU dot products and an online
-// softmax across the wave; used for fp32 inputs, where bf16 MFMA would not meet
-// fp32 accuracy.
+// fp32 kernel: the float32 MFMA core of attn_f32.h, 16 or 32 rows per workgroup; used for
+// fp32 inputs, where bf16 MFMA would not meet fp32 accuracy.
 
 #include <math.h>
 
+#include "attn_f32.h"
 #include "dev_common.h"
 #include "internal.h"
 
@@ -66,22 +66,6 @@ struct AttnArgs {
     int cap;                 // rows this launch may process (row capacity, host bound)
     float scale;             // softmax scale (natural units)
 };
-
-// Row of key index c for KV head g: returns the element offset of that row in
-// either the fresh tensor (fresh = true) or the cached layer.
-template <int D, bool FULL>
-__device__ __forceinline__ size_t kv_row(const AttnArgs& a, int c, int g, bool& fresh) {
-    int pos, r;
-    if (FULL) {
-        pos = c;
-        r = a.rank_l[c];
-    } else {
-        pos = a.U[c];
-        r = a.src_l[c];
-    }
-    fresh = r >= 0;
-    return fresh ? ((size_t)r * a.Hkv + g) * D : (size_t)(g * a.kv_sh + pos * a.kv_st);
-}
 
 // ----------------------------------------------------------------- bf16 MFMA
 
@@ -535,70 +519,39 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
 }
 
 
-// ----------------------------------------------------------------- fp32 VALU
+// ----------------------------------------------------------------- fp32 MFMA
 
-template <int D, bool FULL>
-__global__ __launch_bounds__(64) void attn_f32(AttnArgs a) {
-    constexpr int DPL = D / 64;            // d values owned per lane
-    __shared__ float qs[D];
-    const int t = blockIdx.x, head = blockIdx.y;
+// One workgroup per R (target, head) rows of a KV head (row t*G + hh), the last
+// targets' tiles (the longest contexts) first.
+template <int D, bool FULL, int R>
+__global__ __launch_bounds__(MfmaF32<R>::waves * 64) void attn_f32(AttnArgs a) {
+    extern __shared__ __attribute__((aligned(16))) char f32_lds[];
     const int nR_dev = a.counts[1 + a.layer];
-    if (nR_dev > a.cap && t == 0 && head == 0 && threadIdx.x == 0) atomicOr(a.err, RELAXKV_ERR_ROWS);
-    if (t >= min(nR_dev, a.cap)) return;
-    const int lane = threadIdx.x;
-    const int g = head / a.G;
+    const int nR = min(nR_dev, a.cap);
+    if (nR_dev > a.cap && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+        atomicOr(a.err, RELAXKV_ERR_ROWS);
+    const long nrows = (long)nR * a.G;
+    const long tile = (nrows + R - 1) / R - 1 - blockIdx.x;
+    if (tile < 0) return;
+    const int g = blockIdx.y;
+    const long row = tile * R + threadIdx.x % R;
+    const bool valid = row < nrows;
     const int off = a.R_off[a.layer];
-    const int lim = FULL ? a.R_idx[off + t] : a.R_u[off + t];
-    if (lim < 0) {                                     // empty context: the empty sum
-        float* out = (float*)a.out + ((size_t)t * a.H + head) * D;
-        for (int e = lane; e < D; e += 64) out[e] = 0.f;
-        if (a.lse && lane == 0) a.lse[(size_t)t * a.H + head] = -INFINITY;
-        return;
-    }
-    const float* qn = (const float*)a.q_new;
-    const float* kn = (const float*)a.k_new;
-    const float* vn = (const float*)a.v_new;
-    const float* kc = (const float*)a.kc;
-    const float* vc = (const float*)a.vc;
-    for (int e = lane; e < D; e += 64) qs[e] = qn[((size_t)t * a.H + head) * D + e];
-    __syncthreads();
-
-    float o[DPL];
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) o[i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-    for (int c0 = 0; c0 <= lim; c0 += 64) {
-        const int c = c0 + lane;
-        float s = -INFINITY;
-        const float* vrow = nullptr;
-        if (c <= lim) {
-            bool fresh;
-            const size_t row = kv_row<D, FULL>(a, c, g, fresh);
-            const float* kr = (fresh ? kn : kc) + row;
-            vrow = (fresh ? vn : vc) + row;
-            float acc = 0.f;
-            for (int e = 0; e < D; ++e) acc = fmaf(qs[e], kr[e], acc);
-            s = acc * a.scale;
-        }
-        const float m_new = fmaxf(m_run, wave_max(s));
-        const float alpha = expf(m_run - m_new);
-        const float p = c <= lim ? expf(s - m_new) : 0.f;
-        l_run = l_run * alpha + wave_sum(p);
-#pragma unroll
-        for (int i = 0; i < DPL; ++i) o[i] *= alpha;
-        const int nk = min(64, lim - c0 + 1);
-        for (int j = 0; j < nk; ++j) {
-            const float pj = __shfl(p, j, 64);
-            const float* vj = (const float*)__shfl((long long)vrow, j, 64);
-#pragma unroll
-            for (int i = 0; i < DPL; ++i) o[i] = fmaf(pj, vj[lane + 64 * i], o[i]);
-        }
-        m_run = m_new;
-    }
-    float* out = (float*)a.out + ((size_t)t * a.H + head) * D;
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) out[lane + 64 * i] = o[i] / l_run;
-    if (a.lse && lane == 0) a.lse[(size_t)t * a.H + head] = m_run + logf(l_run);
+    const int32_t* lim_of = FULL ? a.R_idx + off : a.R_u + off;
+    const long last = min(tile * R + R - 1, nrows - 1);
+    const int t = (int)((valid ? row : last) / a.G);
+    const int head = g * a.G + (int)((valid ? row : last) - (long)t * a.G);
+    const int n_keys = max(lim_of[last / a.G], 0) + 1;   // limits ascend with the row
+    const size_t orow = (size_t)t * a.H + head;
+    auto id_of = [&](int c) {
+        const int r = FULL ? a.rank_l[c] : a.src_l[c];
+        return r >= 0 ? r : ~(FULL ? c : a.U[c]);
+    };
+    attn_f32_rows<D, R>(
+        *(AttnF32Lds<D, R>*)f32_lds, (const float*)a.k_new + g * D, (const float*)a.v_new + g * D,
+        (int64_t)a.Hkv * D, (const float*)a.kc + g * a.kv_sh, (const float*)a.vc + g * a.kv_sh, a.kv_st,
+        id_of, n_keys, (const float*)a.q_new + orow * D, lim_of[t], a.scale, valid,
+        (float*)a.out + orow * D, a.lse ? a.lse + orow : nullptr);
 }
 
 constexpr int kNW = RELAXKV_ATTN_WAVES;
@@ -633,7 +586,15 @@ void launch_one(const AttnArgs& a, bool bf16, int n_bound, hipStream_t st) {
         else
             hipLaunchKernelGGL((attn_bf16<D, FULL, kNW, 3>), dim3(nwg), dim3(kNW * 64), 0, st, a);
     } else {
-        hipLaunchKernelGGL((attn_f32<D, FULL>), dim3(n_bound, a.H), dim3(64), 0, st, a);
+        const long rows = (long)n_bound * a.G;
+        auto go = [&](auto kernel, int r, int waves, size_t lds) {
+            hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + r - 1) / r), a.Hkv), dim3(waves * 64), lds,
+                               st, a);
+        };
+        if (attn_f32_small(rows, a.Hkv))
+            go(attn_f32<D, FULL, 16>, 16, MfmaF32<16>::waves, sizeof(AttnF32Lds<D, 16>));
+        else
+            go(attn_f32<D, FULL, 32>, 32, MfmaF32<32>::waves, sizeof(AttnF32Lds<D, 32>));
     }
 }
 

@@ -21,10 +21,11 @@
 // - every split writes its normalised partial output (bf16) and its row
 //   log2-sum-exp; qattn_merge combines the splits with weights
 //   exp2(lse_s - max) in a fixed order and writes O and the natural-log LSE.
-// fp32 path: one wave per (token, head), VALU dot products over all keys.
+// fp32 path: the float32 MFMA core of attn_f32.h, 16 or 32 (token, head) rows per workgroup.
 
 #include <math.h>
 
+#include "attn_f32.h"
 #include "dev_common.h"
 #include "internal.h"
 
@@ -478,57 +479,24 @@ __global__ __launch_bounds__(D) void qattn_merge_fixed(const uint16_t* __restric
     if (lse && e == 0) lse[th] = (M + __log2f(z)) * kLn2;
 }
 
-// fp32: one wave per (token, head) over all T + t + 1 keys.
-template <int D>
-__global__ __launch_bounds__(64) void qattn_f32(const float* __restrict__ q,
-                                                const float* __restrict__ kc,
-                                                const float* __restrict__ vc,
-                                                const float* __restrict__ kq,
-                                                const float* __restrict__ vq, KvStrides ks,
-                                                int T, int H, int Hkv, int G, float scale,
-                                                float* __restrict__ out, float* __restrict__ lse) {
-    constexpr int DPL = D / 64;
-    __shared__ float qs[D];
-    const int t = blockIdx.x, h = blockIdx.y, lane = threadIdx.x;
-    const int g = h / G;
-    for (int e = lane; e < D; e += 64) qs[e] = q[((size_t)t * H + h) * D + e];
-    __syncthreads();
-    float o[DPL];
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) o[i] = 0.f;
-    float m_run = -INFINITY, l_run = 0.f;
-    const int nk = T + t + 1;
-    for (int c0 = 0; c0 < nk; c0 += 64) {
-        const int c = c0 + lane;
-        float s = -INFINITY;
-        const float* vrow = nullptr;
-        if (c < nk) {
-            const int64_t ce = g * ks.head + c * ks.token;          // cache row element offset
-            const float* krow = c < T ? kc + ce : kq + ((size_t)(c - T) * Hkv + g) * D;
-            vrow = c < T ? vc + ce : vq + ((size_t)(c - T) * Hkv + g) * D;
-            float acc = 0.f;
-            for (int e = 0; e < D; ++e) acc = fmaf(qs[e], krow[e], acc);
-            s = acc * scale;
-        }
-        const float m_new = fmaxf(m_run, wave_max(s));
-        const float alpha = expf(m_run - m_new);
-        const float p = c < nk ? expf(s - m_new) : 0.f;
-        l_run = l_run * alpha + wave_sum(p);
-#pragma unroll
-        for (int i = 0; i < DPL; ++i) o[i] *= alpha;
-        const int cnt = min(64, nk - c0);
-        for (int j = 0; j < cnt; ++j) {
-            const float pj = __shfl(p, j, 64);
-            const float* vj = (const float*)__shfl((long long)vrow, j, 64);
-#pragma unroll
-            for (int i = 0; i < DPL; ++i) o[i] = fmaf(pj, vj[lane + 64 * i], o[i]);
-        }
-        m_run = m_new;
-    }
-    float* orow = out + ((size_t)t * H + h) * D;
-#pragma unroll
-    for (int i = 0; i < DPL; ++i) orow[lane + 64 * i] = o[i] / l_run;
-    if (lse && lane == 0) lse[(size_t)t * H + h] = m_run + logf(l_run);
+// fp32: one workgroup per R (token, head) rows of a KV head (row t*G + hh); key c
+// is cache row c below T and query token c - T from there, row t's last key T + t.
+template <int D, int R>
+__global__ __launch_bounds__(MfmaF32<R>::waves * 64) void qattn_f32(
+    const float* __restrict__ q, const float* __restrict__ kc, const float* __restrict__ vc,
+    const float* __restrict__ kq, const float* __restrict__ vq, KvStrides ks, int T, int n_rows,
+    int H, int Hkv, int G, float scale, float* __restrict__ out, float* __restrict__ lse) {
+    extern __shared__ __attribute__((aligned(16))) char f32_lds[];
+    const int g = blockIdx.y, row0 = blockIdx.x * R + threadIdx.x % R;
+    const int last = min((int)blockIdx.x * R + R - 1, n_rows - 1);
+    const bool valid = row0 < n_rows;
+    const int row = valid ? row0 : last;
+    const int t = row / G, h = g * G + row - t * G;
+    const size_t orow = (size_t)t * H + h;
+    auto id_of = [&](int c) { return c < T ? ~c : c - T; };
+    attn_f32_rows<D, R>(*(AttnF32Lds<D, R>*)f32_lds, kq + g * D, vq + g * D, (int64_t)Hkv * D,
+                        kc + g * ks.head, vc + g * ks.head, ks.token, id_of, T + last / G + 1,
+                        q + orow * D, T + t, scale, valid, out + orow * D, lse ? lse + orow : nullptr);
 }
 
 int qa_waves(int rows_pad) {
@@ -591,14 +559,21 @@ hipError_t launch_query_attn(const relaxkv_problem& p, int layer, const void* k_
         const float* q = (const float*)p.q + (size_t)layer * q_layer;
         const float* kc = (const float*)k_cache + cache_layer;
         const float* vc = (const float*)v_cache + cache_layer;
-        if (p.d == 128)
-            hipLaunchKernelGGL(qattn_f32<128>, dim3(p.n_query, p.H), dim3(64), 0, st, q, kc, vc,
-                               (const float*)k_q, (const float*)v_q, ks, p.T_c, p.H, p.H_kv, G, scale,
-                               (float*)out, lse_out);
-        else
-            hipLaunchKernelGGL(qattn_f32<64>, dim3(p.n_query, p.H), dim3(64), 0, st, q, kc, vc,
-                               (const float*)k_q, (const float*)v_q, ks, p.T_c, p.H, p.H_kv, G, scale,
-                               (float*)out, lse_out);
+        const int n_rows = p.n_query * G;
+        auto go = [&](auto kernel, int r, int waves, size_t lds) {
+            hipLaunchKernelGGL(kernel, dim3((n_rows + r - 1) / r, p.H_kv), dim3(waves * 64), lds, st, q,
+                               kc, vc, (const float*)k_q, (const float*)v_q, ks, p.T_c, n_rows, p.H,
+                               p.H_kv, G, scale, (float*)out, lse_out);
+        };
+        auto go_d = [&](auto d_t) {
+            constexpr int D = decltype(d_t)::value;
+            if (attn_f32_small(n_rows, p.H_kv))
+                go(qattn_f32<D, 16>, 16, MfmaF32<16>::waves, sizeof(AttnF32Lds<D, 16>));
+            else
+                go(qattn_f32<D, 32>, 32, MfmaF32<32>::waves, sizeof(AttnF32Lds<D, 32>));
+        };
+        if (p.d == 128) go_d(Int<128>{});
+        else go_d(Int<64>{});
         return hipGetLastError();
     }
     const QueryAttnWorkspace w = query_attn_workspace_layout(p);

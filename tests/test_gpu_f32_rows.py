@@ -1,0 +1,64 @@
+"""The float32 kernels at the edges of their tiles: 16- and 32-row attention
+workgroups (the launch rule's two sides), contexts shorter than one key block, one
+key past a round of the waves' blocks, rows that do not fill a tile, empty contexts,
+and fresh rows aligned to 4 bytes only; scores over the same shapes.  Every value
+against the float64 oracle within the fp32 tolerance."""
+
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from harness import Case, assert_close, synthetic_scores
+from paper_2609_33503_amd import relaxkv, synth
+
+pytestmark = pytest.mark.gpu
+
+W = synth.WORKLOADS["tiny-2L-1k-fp32"]
+
+
+def off4(t):
+    """A contiguous copy of t that starts 4 bytes past a 16-byte boundary."""
+    buf = torch.empty(t.numel() + 1, dtype=t.dtype, device=t.device)
+    out = buf[1:].view(t.shape)
+    out.copy_(t)
+    return out
+
+
+# (T, H, H_kv, Qn, targets): the last two launch 32-row workgroups
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("T,H,H_kv,Qn,n", [(5, 1, 1, 1, 3), (33, 3, 1, 5, 33), (257, 10, 2, 3, 60),
+                                           (600, 4, 4, 21, 129), (300, 32, 32, 130, 150),
+                                           (540, 33, 11, 170, 151)])
+def test_f32_rows(gpu_lib, T, H, H_kv, Qn, n, d):
+    w = synth.shrink(W, L=2, T_c=T, H=H, H_kv=H_kv, Qn=Qn, d=d)
+    case = Case(w, ratio=0.3)
+    a_ref, _, _ = case.oracle_scores()
+    assert_close(case.gpu_scores().cpu().numpy(), a_ref, w, "scores")
+    a = synthetic_scores(2, T, seed=T)
+    anchors = oracle.select(a.astype(np.float64), case.k)
+    assert np.array_equal(case.gpu_select(torch.from_numpy(a).cuda()), anchors)
+    P = np.sort(np.random.default_rng(n).choice(T, size=n, replace=False))
+    t = torch.zeros(T, dtype=torch.int32, device="cuda")
+    t[:n] = torch.from_numpy(P.astype(np.int32)).cuda()
+    case.req.build_sets_global(case.sets, t, torch.tensor([n], dtype=torch.int32, device="cuda"))
+    case.sets.counts_to_host()
+    ref = oracle.build_sets_global(anchors, T, P)
+    fresh = [off4(x) for x in case.fresh(1, P)]
+    ts = sorted(set([0, 1, n - 1, n // 2] + np.random.default_rng(1).integers(0, n, 30).tolist()))
+    for mode, cm in (("union", relaxkv.CONTEXT_UNION), ("full", relaxkv.CONTEXT_FULL)):
+        out, lse = case.gpu_attn(1, fresh, n, cm)
+        O_ref, lse_ref = case.oracle_attn(1, ref, fresh, mode=mode, targets=ts)
+        empty = np.isneginf(lse_ref)
+        got, got_lse = out[ts].cpu().numpy(), lse[ts].cpu().numpy()
+        assert np.array_equal(np.isneginf(got_lse), empty) and not got[empty].any()
+        assert_close(got[~empty], O_ref[~empty], w, f"{mode} out")
+        assert_close(got_lse[~empty], lse_ref[~empty], w, f"{mode} lse")
+    k_q, v_q = (off4(x) for x in synth.make_query_kv(w, 1, "cuda"))
+    out = torch.empty(Qn, H, d, device="cuda")
+    lse = torch.empty(Qn, H, device="cuda")
+    case.req.query_attn(1, case.kc, case.vc, k_q, v_q, out, lse)
+    O_ref, lse_ref = oracle.query_attn(*(synth.to_f64(x) for x in (case.q[1], case.kc[1], case.vc[1],
+                                                                   k_q, v_q)))
+    assert_close(out.cpu().numpy(), O_ref, w, "query out")
+    assert_close(lse.cpu().numpy(), lse_ref, w, "query lse")
