@@ -4,8 +4,8 @@
 //
 // bf16 path (bf16 MFMA, fp32 accumulation).  Per layer l and KV head g the
 // Qn*G query rows that share g form one row set.  A workgroup takes one
-// (l, g, split of contiguous keys: 4096 in the statistics pass, 4096 or 8192 in
-// the column-sum pass): it stages the row set into LDS once (fragment-major),
+// (l, g, split of contiguous keys: up to 4096 in the statistics pass, up to 8192 in
+// the column-sum pass, see pass_split): it stages the row set into LDS once (fragment-major),
 // and each of its waves loads its own 32-key blocks from HBM straight into
 // registers and runs every 32-row block against them, so K never passes
 // through LDS (in the column-sum pass a wave holds two key blocks, so a query
@@ -519,6 +519,9 @@ __global__ __launch_bounds__(256) void score_pool(const float* __restrict__ part
         const int i = blk * kFinKeys + e * 256 + tid;
         if (i < T) {
             float p = 0.f;
+            // eight independent loads in flight, summed in order: 15.8 -> 5.2 us at 32
+            // layers of 8192 keys and 8 KV heads, 22.2 -> 10.5 us at 40 of 32768
+#pragma unroll 8
             for (int j = 0; j < n_part; ++j) p += part[((size_t)l * n_part + j) * T + i];
             p *= inv_hq;
             scores[(size_t)l * T + i] = p;
@@ -581,17 +584,38 @@ void launch_finalize(const relaxkv_problem& p, const ScoreWorkspace& w, char* ws
     hipLaunchKernelGGL(score_minmax, grid, dim3(256), 0, st, (const float2*)mm, w.n_blk, p.T_c, scores);
 }
 
-// Keys per column-sum workgroup: 4096 or 8192, whichever needs fewer key-steps
-// per CU on the chip's 256 CUs (ceil(workgroups / 256) * split), the larger one
-// on a tie (fewer query stagings and workgroup starts).  Each key's column sum
-// does not depend on the split, so neither do the scores.
-int colsum_split(const relaxkv_problem& p) {
-    constexpr long kCUs = 256;
-    auto cost = [&](long split) {
+// Keys per workgroup of a scoring pass: the power of two in [512, max_split] that
+// needs the fewest key-steps per CU, ceil(workgroups / 256) * (keys + 900), the
+// larger one on a tie.  The 900 keys stand for what a workgroup costs before its
+// first key (the start and the staging of its query rows, 6-9 us, against 3-5 us
+// for 512 keys at 96-256 query rows).  Measured, self-contained scores in us with
+// the statistics pass at 512 / 1024 / 2048 / 4096 keys: 4 layers of 3000 keys (8 KV
+// heads, 64 query tokens) 68 / 72 / 82 / 93, 12 layers 100 / 95 / 87 / 95, 32 layers
+// 167 / 140 / 141 / 124, 40 layers of 4096 (40 heads) 364 / 316 / 308 / 333; the
+// column-sum pass runs in the same order.
+int pass_split(const relaxkv_problem& p, int max_split) {
+    constexpr long kCUs = 256, kStart = 900;
+    long best = 0, best_cost = 0;
+    for (long split = max_split; split >= 512; split /= 2) {
         const long wg = (p.T_c + split - 1) / split * (long)p.H_kv * p.L;
-        return (wg + kCUs - 1) / kCUs * split;
-    };
-    return cost(2 * kKeysPerSplit) <= cost(kKeysPerSplit) ? 2 * kKeysPerSplit : kKeysPerSplit;
+        const long keys = split < p.T_c ? split : (p.T_c + 511) / 512 * 512;
+        const long cost = (wg + kCUs - 1) / kCUs * (keys + kStart);
+        if (!best || cost < best_cost) {
+            best = split;
+            best_cost = cost;
+        }
+    }
+    return (int)best;
+}
+
+// Column sums: each key's does not depend on the split, so neither do the scores.
+int colsum_split(const relaxkv_problem& p) { return pass_split(p, 2 * kKeysPerSplit); }
+
+// Statistics: the split sets the order in which a row's sum is merged, so it is
+// fixed for the contexts of more than one full-size split (their scores are then
+// the same bits whatever the number of layers) and chosen below.
+int stats_split(const relaxkv_problem& p) {
+    return p.T_c > kKeysPerSplit ? kKeysPerSplit : pass_split(p, kKeysPerSplit);
 }
 
 template <int D>
@@ -607,8 +631,8 @@ void launch_passes_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, char*
     constexpr int KNW = RELAXKV_SCORE_KREG_NW, KNKB = RELAXKV_SCORE_KREG_NKB;
     constexpr int CNW = RELAXKV_SCORE_COLSUM_NW, CNKB = RELAXKV_SCORE_COLSUM_NKB;
     static_assert(kKeysPerSplit % (KNW * KNKB * 32) == 0 && kKeysPerSplit % (CNW * CNKB * 32) == 0,
-                  "a split is whole rounds of both passes (the statistics splits are the workspace's n_split)");
-    const int kps = kKeysPerSplit;
+                  "a full-size split is whole rounds of both passes");
+    const int kps = stats_split(p);
     const dim3 kgrid((p.T_c + kps - 1) / kps, p.H_kv, p.L);
     if (!p.q_lse) {
         hipLaunchKernelGGL((score_stats_kreg<D, KNW, KNKB>), kgrid, dim3(KNW * 64), 0, st, q, kc,
@@ -660,7 +684,8 @@ ScoreWorkspace score_workspace_layout(const relaxkv_problem& p) {
     const int G = p.H / p.H_kv;
     const bool bf = p.dtype == RELAXKV_DTYPE_BF16;
     w.rows_pad = round_up32(p.n_query * G);
-    w.n_split = (p.T_c + kKeysPerSplit - 1) / kKeysPerSplit;
+    const int kps = stats_split(p);
+    w.n_split = (p.T_c + kps - 1) / kps;
     w.n_part = bf ? p.H_kv : 1;
     w.part_off = 0;
     size_t off = al((size_t)p.L * w.n_part * p.T_c * sizeof(float));
