@@ -86,25 +86,30 @@ __device__ __forceinline__ float pair_sum(float x) {
     return __uint_as_float(r[0]) + __uint_as_float(r[1]);
 }
 
-// NW waves as NW / KG groups of 32 rows times KG key groups.
-// KG = 1 (launches with tiles for every CU): 64-key steps, one barrier per step.
-// The fills of step j+3 and the indices of step j+4 are issued right after the
-// barrier of step j, so every fill has two steps of compute to land.
-// KG = 3 (launches with few tiles): a tile is a third of the rows, so there are
-// three times as many workgroups, and each step brings 96 keys through a 3-deep
-// ring, 32 for each key group; the key groups keep their own running max, sum and
-// output, which are combined through LDS after the last step like key splits.
-// The same fills serve a third of the rows, so a step costs more per row; it pays
-// where CUs would stay idle (see attn_key_groups).
+// NW waves as NW / KG groups of 32 rows times KG key groups; 64 keys per key group
+// and step, one barrier per step.
+// KG = 1 (12 waves; launches with tiles for every CU): a 4-deep ring.  The fills of
+// step j+3 and the indices of step j+4 are issued right after the barrier of step
+// j, so every fill has two steps of compute to land.
+// KG = 2 (8 waves; launches with few tiles): a tile is a third of the rows, so
+// there are three times as many workgroups, and each step brings 128 keys through a
+// 2-deep ring, half for each key group (the fills of step j+1 go out after the
+// barrier of step j; the rows of a KV head are shared by its workgroups, so most
+// come from L2); the key groups keep their own running max, sum and output, which
+// are combined through LDS after the last step like key splits.  The same fills
+// serve a third of the rows, so a step costs more per row; it pays where CUs would
+// stay idle (see attn_key_groups).
 template <int D, bool FULL, int NW, int KG>
 __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
-    static_assert(KG == 1 || KG == 3, "key groups");
-    constexpr int NST = KG == 1 ? 4 : 3;   // ring depth
-    constexpr int TKG = KG == 1 ? 64 : 32; // keys per step of a key group
+    static_assert(KG == 1 || KG == 2, "key groups");
+    constexpr int NST = KG == 1 ? 4 : 2;   // ring depth
+    constexpr int TKG = 64;                // keys per step of a key group
     constexpr int NKB = TKG / 32;          // 32-key blocks of it
     constexpr int TK = KG * TKG;           // keys per step
     constexpr int RG = NW / KG;            // row groups
-    constexpr int IXP = (TK + 63) / 64;    // index loads per step and list
+    constexpr int IXP = TK / 64;           // index loads per step and list
+    constexpr int NIX = 4;                 // index ring depth
+    constexpr int IXA = KG == 1 ? NST : 2; // steps the indices are issued ahead of
     constexpr int KS = D / 16;             // k-steps of the QK^T contraction
     constexpr int DB = D / 32;             // 32-wide d blocks of O^T
     constexpr int ROWB = 2 * D;            // tile row bytes
@@ -116,8 +121,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     constexpr int NWAIT_TAIL = 2 * (NL / NW);  // fills per step of the least busy wave
     __shared__ __attribute__((aligned(1024))) uint16_t Kt[NST][TK * D];
     __shared__ __attribute__((aligned(1024))) uint16_t Vt[NST][TK * D];
-    __shared__ __attribute__((aligned(256))) int32_t Ix[NST][2][IXP * 64];   // [U or rank, src]
-    auto ring = [](int m) { return NST == 4 ? m & 3 : m % NST; };
+    __shared__ __attribute__((aligned(256))) int32_t Ix[NIX][2][IXP * 64];   // [U or rank, src]
 
     __shared__ int s_pick;
 
@@ -139,7 +143,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     // last workgroup to finish returns the counters to zero for the next launch
     // of this layer and mode (it is counted after its pick was handed out, which
     // the pick's returned value proves, so every other pick happened before).
-    // KG = 3: workgroup i takes head i mod Hkv, heaviest tiles first (also one head
+    // KG = 2: workgroup i takes head i mod Hkv, heaviest tiles first (also one head
     // per XCD at 8 heads); such a launch is one to three rounds of workgroups, so
     // the spread of the XCDs' clocks costs less than the counters' round trips.
     int pick = blockIdx.x;
@@ -237,11 +241,11 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
             int ww = w / IXP;
             asm volatile("" : "+s"(ww));
             const int part = IXP == 1 ? 0 : w % IXP * 64;
-            // (KG = 3: clamped to the list, which is known before the tile's limits; the
+            // (KG = 2: clamped to the list, which is known before the tile's limits; the
             // fills then clamp to cmax)
             const int c = min(m * TK + part + lane, KG == 1 ? cmax : idx_max);
             const int32_t* src = FULL ? srcmap + c : (ww == 0 ? a.U + c : srcmap + c);
-            fill_lds4(src, lds_addr(&Ix[ring(m)][ww][part]));
+            fill_lds4(src, lds_addr(&Ix[m & (NIX - 1)][ww][part]));
         }
     };
     // The lane's tile row and swizzled chunk offset (elements) in each of its
@@ -254,7 +258,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         f_choff[i] = (uint32_t)(((lane % CH) ^ tile_swz<D>(f_row[i])) << 3);
     }
     auto issue_rows = [&](int m) {
-        const int st = ring(m);
+        const int st = m & (NST - 1), ix = m & (NIX - 1);
 #pragma unroll
         for (int i = 0; i < PPW; ++i) {
             const int j = w + i * NW;
@@ -264,8 +268,8 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
                 asm volatile("" : "+v"(row), "+v"(choff));
                 if (KG > 1) row = min(row, cmax - m * TK);
                 const int c = m * TK + row;
-                int pos = FULL ? min(c, cmax) : Ix[st][0][row];
-                int r = Ix[st][FULL ? 0 : 1][row];
+                int pos = FULL ? min(c, cmax) : Ix[ix][0][row];
+                int r = Ix[ix][FULL ? 0 : 1][row];
                 asm volatile("" : "+v"(pos), "+v"(r));      // both read, then selected
                 // (the empty asm statements keep the compiler from turning the
                 // fresh/cached choice into a divergent branch)
@@ -291,7 +295,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int v_base1 = (rl + 8) * ROWB | ((cl ^ tile_swz<D>(rl + 8)) << 4) | ((lane & 1) << 3);
 
 #pragma unroll
-    for (int m = 0; m < NST; ++m)
+    for (int m = 0; m < IXA; ++m)
         if (KG > 1 || m < S) issue_idx(m);
     wait_loads_barrier<0>();
     if (KG > 1) use_q();
@@ -307,11 +311,11 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         // its loads are outstanding as it issued after them: the fills of steps
         // j+1 and j+2 (at least NWAIT loads while both steps exist), only those
         // of step j+1 near the end (at least NWAIT_TAIL), none in the last step.
-        // (3-deep ring: one step less; only the fills of step j+1 may be in flight.)
+        // (2-deep ring: nothing was issued after the fills of step j.)
         if (NST == 4 && j + 2 < S) wait_loads_barrier<NWAIT>();
-        else if (j + 1 < S) wait_loads_barrier<NWAIT_TAIL>();
+        else if (NST == 4 && j + 1 < S) wait_loads_barrier<NWAIT_TAIL>();
         else wait_loads_barrier<0>();
-        if (j + NST < S) issue_idx(j + NST);
+        if (j + IXA < S) issue_idx(j + IXA);
         if (j + NST - 1 < S) issue_rows(j + NST - 1);
         // A step whose keys all lie past every limit of the wave's rows adds
         // exact zeros to them (p = 0): the wave only keeps the ring moving.
@@ -321,7 +325,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         f32x16 s[NKB];
         {
             // (the stage and key-group offsets leave the swizzled bits alone)
-            int kbo = k_base + ring(j) * (TK * D * 2) + (KG == 1 ? 0 : kg * TKG * ROWB);
+            int kbo = k_base + (j & (NST - 1)) * (TK * D * 2) + (KG == 1 ? 0 : kg * TKG * ROWB);
             asm volatile("" : "+v"(kbo));
             const char* kst = (const char*)Kt[0];
 #pragma unroll
@@ -433,7 +437,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
         {
             // LDS byte addresses of the lane's two V rows in this step's tile: the
             // tile base and stage only set bits above the swizzled chunk bits.
-            const uint32_t vstage = lds_addr(Vt[0]) + (uint32_t)ring(j) * (TK * D * 2) +
+            const uint32_t vstage = lds_addr(Vt[0]) + (uint32_t)(j & (NST - 1)) * (TK * D * 2) +
                                     (KG == 1 ? 0u : (uint32_t)(kg * TKG * ROWB));
             uint32_t vb0 = v_base0 + vstage, vb1 = v_base1 + vstage;
             asm volatile("" : "+v"(vb0), "+v"(vb1));
@@ -463,35 +467,31 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
 
     float l_tot = pair_sum(l_run);
     if constexpr (KG > 1) {
-        // Key groups 1 and 2 hand their (O, m, l) to the row group's first wave
-        // through the ring's LDS (free: the last fills were waited for and read).
+        // Key group 1 hands its (O, m, l) to the row group's first wave through the
+        // ring's LDS (free: the last fills were waited for and read).
         constexpr int OW = DB * 16 * 64;                   // floats of one wave's O
-        static_assert((RG * (OW + 128)) * 4 <= (int)sizeof(Kt), "one key group's hand-over per tensor");
+        static_assert(RG * OW * 4 <= (int)sizeof(Kt) && RG * 512 <= (int)sizeof(Vt), "hand-over");
         __syncthreads();
+        float* mo = (float*)&Kt[0][0] + rg * OW + lane;
+        float* ml = (float*)&Vt[0][0] + rg * 128 + lane;
         if (kg > 0) {
-            float* mo = (float*)(kg == 1 ? &Kt[0][0] : &Vt[0][0]) + rg * (OW + 128) + lane;
 #pragma unroll
             for (int db = 0; db < DB; ++db)
 #pragma unroll
                 for (int v = 0; v < 16; ++v) mo[(db * 16 + v) * 64] = o[db][v];
-            mo[OW] = m_run;
-            mo[OW + 64] = l_tot;
+            ml[0] = m_run;
+            ml[64] = l_tot;
         }
         __syncthreads();
         if (kg > 0) return;
-        const float* p1 = (const float*)&Kt[0][0] + rg * (OW + 128) + lane;
-        const float* p2 = (const float*)&Vt[0][0] + rg * (OW + 128) + lane;
-        const float m1 = p1[OW], m2 = p2[OW];
-        const float m = fmaxf(m_run, fmaxf(m1, m2));
+        const float m1 = ml[0], m = fmaxf(m_run, m1);
         const float w0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m);
         const float w1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - m);
-        const float w2 = m2 == -INFINITY ? 0.f : fast_exp2(m2 - m);
 #pragma unroll
         for (int db = 0; db < DB; ++db)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                o[db][v] = o[db][v] * w0 + p1[(db * 16 + v) * 64] * w1 + p2[(db * 16 + v) * 64] * w2;
-        l_tot = l_tot * w0 + p1[OW + 64] * w1 + p2[OW + 64] * w2;
+            for (int v = 0; v < 16; ++v) o[db][v] = o[db][v] * w0 + mo[(db * 16 + v) * 64] * w1;
+        l_tot = l_tot * w0 + ml[64] * w1;
         m_run = m;
     }
     leave();
@@ -556,19 +556,24 @@ __global__ __launch_bounds__(MfmaF32<R>::waves * 64) void attn_f32(AttnArgs a) {
 
 constexpr int kNW = RELAXKV_ATTN_WAVES;
 static_assert(kAttnRows == kNW * 32, "rows per workgroup");
+constexpr int kNW2 = 8;                    // waves of the two-key-group kernel
+constexpr int kAttnRows2 = kNW2 / 2 * 32;  // its rows per workgroup
 
-// Key groups of a launch of `rows` (target, head) rows per KV head: one while
-// whole tiles outnumber the chip's 256 CUs, three otherwise.  Up to there every
-// tile has a CU to itself and the launch lasts as long as the longest tile's
-// steps, so a third of the rows and of the steps per workgroup is shorter; past
-// it the extra fills per row count.  Measured, one against three key groups, d
-// 128, 8 KV heads: 24 tiles (1.5K context) 28.1 / 20.4 us, 104 (8K) 163 / 89,
-// 160 (8K) 165 / 102, 264 (8K) 175 / 169, 264 (16K) 345 / 315, 312 (8K) 185 / 191,
-// 408 (8K) 206 / 249; d 64, 2 KV heads: 140 (5K, full prefix) 117 / 63, 312 (8K, 8
-// KV heads) 125 / 128.
-int attn_key_groups(long rows, int Hkv) {
+// Key groups of a launch of `rows` (target, head) rows per KV head, by its count of
+// 384-row tiles: two up to 5/4 of the chip's 256 CUs at d 128, up to three times
+// them at d 64 (whose smaller workgroups fit a CU twice), one past that.  While
+// every tile has a CU to itself the launch lasts as long as the longest tile's
+// steps, so a third of the rows and half of the steps per workgroup is shorter;
+// past it the extra fills per row count.  Measured in us, one against two key
+// groups, 8 KV heads: d 128: 24 tiles (1.5K context) 28.4 / 17.8, 104 (8K) 163 / 82,
+// 264 (8K) 173 / 152, 264 (16K) 341 / 289, 312 (8K) 181 / 174, 328 (9K) 199 / 200,
+// 352 (8K) 186 / 199, 552 (16K) 493 / 576; d 64: 104 (8K) 118 / 59, 264 (8K) 128 /
+// 92, 408 (8K) 138 / 126, 568 (16K) 318 / 311, 752 (16K) 419 / 407, 1400 (32K)
+// 1420 / 1466.
+int attn_key_groups(long rows, int Hkv, int d) {
     constexpr long kCUs = 256;
-    return (rows + kAttnRows - 1) / kAttnRows * Hkv <= kCUs ? 3 : 1;
+    const long tiles = (rows + kAttnRows - 1) / kAttnRows * Hkv;
+    return tiles <= (d == 128 ? kCUs * 5 / 4 : kCUs * 3) ? 2 : 1;
 }
 
 template <int D, bool FULL>
@@ -576,15 +581,15 @@ void launch_one(const AttnArgs& a, bool bf16, int n_bound, hipStream_t st) {
     n_bound = n_bound > 0 ? n_bound : 1;                 // workgroup 0 still checks the count
     if (bf16) {
         const long rows = (long)n_bound * a.G;
-        const int kg = attn_key_groups(rows, a.Hkv);
-        const int tr = kAttnRows / kg;                   // rows of a tile
+        const int kg = attn_key_groups(rows, a.Hkv, D);
+        const int tr = kg == 1 ? kAttnRows : kAttnRows2; // rows of a tile
         const int nwg = (int)((rows + tr - 1) / tr) * a.Hkv;
         // One workgroup per tile of the bound, plus an eighth spare where they take
         // their tiles from the counters (they exit once every one is exhausted).
         if (kg == 1)
             hipLaunchKernelGGL((attn_bf16<D, FULL, kNW, 1>), dim3(nwg + nwg / 8), dim3(kNW * 64), 0, st, a);
         else
-            hipLaunchKernelGGL((attn_bf16<D, FULL, kNW, 3>), dim3(nwg), dim3(kNW * 64), 0, st, a);
+            hipLaunchKernelGGL((attn_bf16<D, FULL, kNW2, 2>), dim3(nwg), dim3(kNW2 * 64), 0, st, a);
     } else {
         const long rows = (long)n_bound * a.G;
         auto go = [&](auto kernel, int r, int waves, size_t lds) {

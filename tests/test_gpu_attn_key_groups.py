@@ -1,6 +1,6 @@
-"""The bf16 attention on both sides of its key-group rule: launches of at most 256
-384-row tiles split each workgroup's keys over three wave groups, larger ones do
-not.  Sampled targets (the first ones, whose contexts end inside the first key
+"""The bf16 attention on both sides of its key-group rule: launches of at most 320
+384-row tiles (768 at d 64) split each workgroup's keys over two wave groups, larger
+ones do not.  Sampled targets (the first ones, whose contexts end inside the first key
 group's keys, and the last of a ragged tile among them) against the oracle, and
 the work counters are zero afterwards on both sides."""
 
@@ -17,11 +17,13 @@ pytestmark = pytest.mark.gpu
 W = synth.WORKLOADS["llama8b-8k"]
 
 
-# 32 KV heads: 8 tiles each make 256.  G = 4 at 768 targets fills them exactly.
+# G = 4: 960 targets of 32 KV heads fill 320 tiles, 1152 of 64 heads 768.
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("T,G,n", [(97, 1, 97), (96, 3, 33), (801, 4, 768), (801, 4, 769), (1100, 5, 700)])
-def test_key_groups(gpu_lib, T, G, n, d):
-    w = synth.shrink(W, L=2, T_c=T, H=32 * G, H_kv=32, d=d, Qn=2)
+@pytest.mark.parametrize("T,G,H_kv,n", [(97, 1, 32, 97), (96, 3, 32, 33), (129, 2, 5, 128), (1000, 4, 32, 960),
+                                        (1000, 4, 32, 961), (1100, 5, 32, 700), (1200, 4, 64, 1152),
+                                        (1200, 4, 64, 1153)])
+def test_key_groups(gpu_lib, T, G, H_kv, n, d):
+    w = synth.shrink(W, L=2, T_c=T, H=H_kv * G, H_kv=H_kv, d=d, Qn=2)
     case = Case(w, ratio=0.4)
     a = synthetic_scores(2, T, seed=T)
     anchors = oracle.select(a.astype(np.float64), case.k)
