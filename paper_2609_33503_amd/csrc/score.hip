@@ -91,21 +91,49 @@ __device__ __forceinline__ void stage_rows(bf16x8* Qs, const uint16_t* __restric
     }
 }
 
+// A row's log2-sum-exp from its splits' (m, sum) pairs (n_split of them, rows_pad apart).
+__device__ __forceinline__ float merge_stats(const float2* __restrict__ s, int n_split,
+                                             int rows_pad) {
+    float M = -INFINITY;
+    for (int j = 0; j < n_split; ++j) M = fmaxf(M, s[(size_t)j * rows_pad].x);
+    float Z = 0.f;
+    for (int j = 0; j < n_split; ++j) {
+        const float2 v = s[(size_t)j * rows_pad];
+        Z += v.y * fast_exp2(v.x - M);
+    }
+    return M + __log2f(Z);
+}
+
+// Up to this many splits the column-sum workgroups merge the statistics of their
+// rows themselves while they stage them, which saves a launch (4-5 us); past it a
+// launch of its own merges each row once.
+constexpr int kMergeInline = 8;
+
 // The accumulator start values of the column-sum pass: Ls[rb][hf][i] = -lse2 / sl2
 // of row rc0 + 32 rb + 8 (i / 4) + 4 hf + i % 4, the row that element i of an
 // S = Q K^T accumulator of row block rb holds in lane half hf; -inf for padding
-// rows (their probabilities are then exp2(-inf) = 0).
+// rows (their probabilities are then exp2(-inf) = 0).  From q_lse if given, else
+// from the merged lse2 or, with n_merge > 0, from the statistics of n_merge splits
+// that lse2 then points at.
 __device__ __forceinline__ void stage_lse(float (*Ls)[2][16], int nt, int l, int g, int Qn,
                                           int H, int Hkv, int G, int n_rows, int rows_pad,
                                           int rc0, int nrb, float sl2,
                                           const float* __restrict__ lse2,
-                                          const float* __restrict__ q_lse) {
-    for (int f = threadIdx.x; f < nrb * 32; f += nt) {
+                                          const float* __restrict__ q_lse, int n_merge) {
+    // (the index is opaque, so that nothing derived from it stays live across the
+    // caller's main loop)
+    int f0 = threadIdx.x;
+    asm volatile("" : "+v"(f0));
+    for (int f = f0; f < nrb * 32; f += nt) {
         const int rb = f >> 5, hh = (f >> 4) & 1, i = f & 15;
         const int row = rc0 + 32 * rb + 8 * (i >> 2) + 4 * hh + (i & 3);
         const float x = row >= n_rows ? INFINITY
                         : q_lse ? q_lse[((size_t)l * Qn + row / G) * H + g * G + row % G] * kLog2e
-                                : lse2[((size_t)l * Hkv + g) * rows_pad + row];
+                        : n_merge
+                            ? merge_stats((const float2*)lse2 +
+                                              ((size_t)l * Hkv + g) * n_merge * rows_pad + row,
+                                          n_merge, rows_pad)
+                            : lse2[((size_t)l * Hkv + g) * rows_pad + row];
         Ls[rb][hh][i] = -x / sl2;
     }
 }
@@ -146,7 +174,8 @@ template <int D, int NW, int NKB>
 __global__ __launch_bounds__(NW * 64) void score_colsum_kreg(
     const uint16_t* __restrict__ q, const uint16_t* __restrict__ kc, KvStrides ks, int T, int Qn, int H,
     int Hkv, int G, int n_rows, int rows_pad, int keys_per_split, float sl2,
-    const float* __restrict__ lse2, const float* __restrict__ q_lse, float* __restrict__ part) {
+    const float* __restrict__ lse2, const float* __restrict__ q_lse, int n_merge,
+    float* __restrict__ part) {
     constexpr int KS = D / 16;                      // k-steps of the dot product
     constexpr int NRB = kKregRowBlocks;             // row blocks per chunk
     constexpr int KPW = NKB * 32;                   // keys of a wave per round
@@ -169,7 +198,8 @@ __global__ __launch_bounds__(NW * 64) void score_colsum_kreg(
         const int nrb = min(NRB, (rows_pad - rc0) / 32);
         __syncthreads();                             // the previous chunk's reads are done
         stage_rows<D, NW>(Qs, q, l, g, Qn, H, G, n_rows, rc0, nrb);
-        stage_lse(Ls, NW * 64, l, g, Qn, H, Hkv, G, n_rows, rows_pad, rc0, nrb, sl2, lse2, q_lse);
+        stage_lse(Ls, NW * 64, l, g, Qn, H, Hkv, G, n_rows, rows_pad, rc0, nrb, sl2, lse2, q_lse,
+                  n_merge);
         __syncthreads();
 
         // One round: the wave's NKB key blocks (in kfr) against every row block;
@@ -367,15 +397,7 @@ __global__ void score_merge(const float2* __restrict__ stats, int n_groups, int 
         lse2[i] = INFINITY;     // padding rows contribute exp2(-inf) = 0
         return;
     }
-    const float2* s = stats + lg * n_split * rows_pad + row;
-    float M = -INFINITY;
-    for (int j = 0; j < n_split; ++j) M = fmaxf(M, s[(size_t)j * rows_pad].x);
-    float Z = 0.f;
-    for (int j = 0; j < n_split; ++j) {
-        const float2 v = s[(size_t)j * rows_pad];
-        Z += v.y * fast_exp2(v.x - M);
-    }
-    lse2[i] = M + __log2f(Z);
+    lse2[i] = merge_stats(stats + lg * n_split * rows_pad + row, n_split, rows_pad);
 }
 
 // ---------------------------------------------------------------- float32 path
@@ -507,6 +529,7 @@ __global__ __launch_bounds__(kF32Waves * 64) void score_colsum_f32(
 //   score_minmax: every block reduces its layer's block extrema (fixed order)
 //     and rescales its keys to a = (p - min) / (max - min), or 0 when flat.
 constexpr int kFinKeys = 1024;                 // keys per finaliser block (256 threads x 4)
+constexpr int kFinishMaxT = 2048;              // longest context of the one-launch finaliser
 
 __global__ __launch_bounds__(256) void score_pool(const float* __restrict__ part, int n_part,
                                                   int T, float inv_hq, float* __restrict__ scores,
@@ -575,12 +598,67 @@ __global__ __launch_bounds__(256) void score_minmax(const float2* __restrict__ m
     }
 }
 
+// Both steps in one launch for the contexts whose pooled mass one workgroup per layer
+// holds in registers (E positions a thread): the same operations in the same order
+// (extrema do not depend on it).  At 8 layers of 1531 positions 3.8 us against two
+// launches of 4; one workgroup alone reads a layer's partial sums slowly, so at 8192
+// positions and 8 KV heads it takes 28 us against 10 for the two.
+template <int E>
+__global__ __launch_bounds__(1024) void score_finish(const float* __restrict__ part, int n_part,
+                                                     int T, float inv_hq,
+                                                     float* __restrict__ scores) {
+    __shared__ float red_lo[16], red_hi[16];
+    const int l = blockIdx.x, tid = threadIdx.x;
+    float p[E];
+#pragma unroll
+    for (int e = 0; e < E; ++e) p[e] = 0.f;
+    const float* pl = part + (size_t)l * n_part * T;
+#pragma unroll 4
+    for (int j = 0; j < n_part; ++j)
+#pragma unroll
+        for (int e = 0; e < E; ++e) p[e] += pl[(size_t)j * T + min(e * 1024 + tid, T - 1)];
+    float lo = INFINITY, hi = -INFINITY;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {                        // (positions past T repeat the last one)
+        p[e] *= inv_hq;
+        lo = fminf(lo, p[e]);
+        hi = fmaxf(hi, p[e]);
+    }
+    lo = -wave_max(-lo);
+    hi = wave_max(hi);
+    if ((tid & 63) == 0) {
+        red_lo[tid >> 6] = lo;
+        red_hi[tid >> 6] = hi;
+    }
+    __syncthreads();
+    lo = red_lo[0];
+    hi = red_hi[0];
+#pragma unroll
+    for (int i = 1; i < 16; ++i) {
+        lo = fminf(lo, red_lo[i]);
+        hi = fmaxf(hi, red_hi[i]);
+    }
+    const bool flat = !(hi > lo);
+    const float span = hi - lo;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+        const int i = e * 1024 + tid;
+        if (i < T) scores[(size_t)l * T + i] = flat ? 0.f : (p[e] - lo) / span;
+    }
+}
+
 void launch_finalize(const relaxkv_problem& p, const ScoreWorkspace& w, char* ws, float* scores,
                      hipStream_t st) {
+    const float inv_hq = 1.0f / ((float)p.H * (float)p.n_query);
+    auto finish = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(p.L), dim3(1024), 0, st, (const float*)(ws + w.part_off),
+                           w.n_part, p.T_c, inv_hq, scores);
+    };
+    if (p.T_c <= kFinishMaxT) return finish(score_finish<kFinishMaxT / 1024>);
     const dim3 grid(w.n_blk, p.L);
     float2* mm = (float2*)(ws + w.mm_off);
     hipLaunchKernelGGL(score_pool, grid, dim3(256), 0, st, (const float*)(ws + w.part_off), w.n_part,
-                       p.T_c, 1.0f / ((float)p.H * (float)p.n_query), scores, mm, w.n_blk);
+                       p.T_c, inv_hq, scores, mm, w.n_blk);
     hipLaunchKernelGGL(score_minmax, grid, dim3(256), 0, st, (const float2*)mm, w.n_blk, p.T_c, scores);
 }
 
@@ -634,19 +712,22 @@ void launch_passes_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, char*
                   "a full-size split is whole rounds of both passes");
     const int kps = stats_split(p);
     const dim3 kgrid((p.T_c + kps - 1) / kps, p.H_kv, p.L);
+    const bool inline_merge = !p.q_lse && w.n_split <= kMergeInline;
     if (!p.q_lse) {
         hipLaunchKernelGGL((score_stats_kreg<D, KNW, KNKB>), kgrid, dim3(KNW * 64), 0, st, q, kc,
                            kv_strides(p), p.T_c, p.n_query, p.H, p.H_kv, G, n_rows, w.rows_pad, kps, w.n_split,
                            sl2, stats);
         const long n = (long)p.L * p.H_kv * w.rows_pad;
-        hipLaunchKernelGGL(score_merge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                           (const float2*)stats, p.L * p.H_kv, w.n_split, w.rows_pad, n_rows, lse2);
+        if (!inline_merge)
+            hipLaunchKernelGGL(score_merge, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                               (const float2*)stats, p.L * p.H_kv, w.n_split, w.rows_pad, n_rows, lse2);
     }
     const int cps = colsum_split(p);
     const dim3 cgrid((p.T_c + cps - 1) / cps, p.H_kv, p.L);
     hipLaunchKernelGGL((score_colsum_kreg<D, CNW, CNKB>), cgrid, dim3(CNW * 64), 0, st, q, kc,
                        kv_strides(p), p.T_c, p.n_query, p.H, p.H_kv, G, n_rows, w.rows_pad, cps, sl2,
-                       (const float*)lse2, p.q_lse, part);
+                       inline_merge ? (const float*)stats : (const float*)lse2, p.q_lse,
+                       inline_merge ? w.n_split : 0, part);
 }
 
 template <int D>
