@@ -69,6 +69,8 @@ struct AttnArgs {
 
 // ----------------------------------------------------------------- bf16 MFMA
 
+template <int N> struct Int { static constexpr int value = N; };
+
 constexpr float kRescaleSlack = 8.0f;      // log2 units the running max may lag the true max
 constexpr int kXcds = 8;                   // XCDs of an MI355X (workgroup i runs on XCD i mod 8)
 constexpr int kHwRegXccId = 20;            // hardware register holding the wave's XCD index
@@ -167,7 +169,7 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     } else if (pick >= ntiles * Hkv) {
         return;
     }
-    // Counts this workgroup as done with the counters; the last one clears them.
+    // Counts this workgroup as done with the counters (KG = 1); the last one clears them.
     auto leave = [&] {
         if (KG == 1 && threadIdx.x == 0) {
             __threadfence();
@@ -187,13 +189,33 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int r0 = tile * TR;                        // the tile's rows [r0, r1)
     const int r1 = min(r0 + TR, nrows);
     const int t0 = r0 / a.G, t1 = (r1 - 1) / a.G + 1;  // the targets they belong to
-    const int32_t* lim_of = FULL ? a.R_idx + off : a.R_u + off;
-    const int cmin = lim_of[t0];
-    const int cmax = max(lim_of[t1 - 1], 0);
-
     const int tid = threadIdx.x, lane = tid & 63;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int r32 = lane & 31, hf = lane >> 5;
+    // The indices of step m.  KG = 2 clamps them to the list, which is known before
+    // the tile's limits, so that the first ones travel with the limits and the queries
+    // (the fills then clamp to cmax).
+    const int32_t* srcmap = FULL ? a.rank_l : a.src_l;
+    int idx_last = idx_max;
+    auto issue_idx = [&](int m) {
+        if (w < (FULL ? 1 : 2) * IXP) {
+            int ww = w / IXP;
+            asm volatile("" : "+s"(ww));
+            const int part = IXP == 1 ? 0 : w % IXP * 64;
+            const int c = min(m * TK + part + lane, idx_last);
+            const int32_t* src = FULL ? srcmap + c : (ww == 0 ? a.U + c : srcmap + c);
+            fill_lds4(src, lds_addr(&Ix[m & (NIX - 1)][ww][part]));
+        }
+    };
+    if constexpr (KG > 1) {
+#pragma unroll
+        for (int m = 0; m < IXA; ++m) issue_idx(m);
+    }
+    const int32_t* lim_of = FULL ? a.R_idx + off : a.R_u + off;
+    const int cmin = lim_of[t0];
+    const int cmax = max(lim_of[t1 - 1], 0);
+    if (KG == 1) idx_last = cmax;
+
     const float sl2 = a.scale * kLog2e;
     const int rg = KG == 1 ? w : w % RG, kg = KG == 1 ? 0 : w / RG;
 
@@ -233,21 +255,8 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const uint16_t* kcg = (const uint16_t*)a.kc + g * a.kv_sh;
     const uint16_t* vcg = (const uint16_t*)a.vc + g * a.kv_sh;
     const uint32_t kst = (uint32_t)a.kv_st;              // < 2^24 (checked on the host)
-    const int32_t* srcmap = FULL ? a.rank_l : a.src_l;
     const int S = cmax / TK + 1;                     // steps
 
-    auto issue_idx = [&](int m) {
-        if (w < (FULL ? 1 : 2) * IXP) {
-            int ww = w / IXP;
-            asm volatile("" : "+s"(ww));
-            const int part = IXP == 1 ? 0 : w % IXP * 64;
-            // (KG = 2: clamped to the list, which is known before the tile's limits; the
-            // fills then clamp to cmax)
-            const int c = min(m * TK + part + lane, KG == 1 ? cmax : idx_max);
-            const int32_t* src = FULL ? srcmap + c : (ww == 0 ? a.U + c : srcmap + c);
-            fill_lds4(src, lds_addr(&Ix[m & (NIX - 1)][ww][part]));
-        }
-    };
     // The lane's tile row and swizzled chunk offset (elements) in each of its
     // fills: loop invariant.
     int f_row[PPW];
@@ -294,9 +303,11 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     const int v_base0 = rl * ROWB | ((cl ^ tile_swz<D>(rl)) << 4) | ((lane & 1) << 3);
     const int v_base1 = (rl + 8) * ROWB | ((cl ^ tile_swz<D>(rl + 8)) << 4) | ((lane & 1) << 3);
 
+    if constexpr (KG == 1) {
 #pragma unroll
-    for (int m = 0; m < IXA; ++m)
-        if (KG > 1 || m < S) issue_idx(m);
+        for (int m = 0; m < IXA; ++m)
+            if (m < S) issue_idx(m);
+    }
     wait_loads_barrier<0>();
     if (KG > 1) use_q();
 #pragma unroll
@@ -466,56 +477,74 @@ __global__ __launch_bounds__(NW * 64, 1) void attn_bf16(AttnArgs a) {
     }
 
     float l_tot = pair_sum(l_run);
-    if constexpr (KG > 1) {
-        // Key group 1 hands its (O, m, l) to the row group's first wave through the
-        // ring's LDS (free: the last fills were waited for and read).
-        constexpr int OW = DB * 16 * 64;                   // floats of one wave's O
-        static_assert(RG * OW * 4 <= (int)sizeof(Kt) && RG * 512 <= (int)sizeof(Vt), "hand-over");
-        __syncthreads();
-        float* mo = (float*)&Kt[0][0] + rg * OW + lane;
-        float* ml = (float*)&Vt[0][0] + rg * 128 + lane;
-        if (kg > 0) {
-#pragma unroll
-            for (int db = 0; db < DB; ++db)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) mo[(db * 16 + v) * 64] = o[db][v];
-            ml[0] = m_run;
-            ml[64] = l_tot;
-        }
-        __syncthreads();
-        if (kg > 0) return;
-        const float m1 = ml[0], m = fmaxf(m_run, m1);
-        const float w0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m);
-        const float w1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - m);
-#pragma unroll
-        for (int db = 0; db < DB; ++db)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) o[db][v] = o[db][v] * w0 + mo[(db * 16 + v) * 64] * w1;
-        l_tot = l_tot * w0 + ml[64] * w1;
-        m_run = m;
-    }
-    leave();
-    if (!valid) return;
     const bool empty = lim < 0;
-    const float inv = empty ? 0.f : 1.0f / l_tot;
     // (t, head) row index: below T_c * H <= 2^32, and one register where a 64-bit
     // product held across the loop would take two
     const uint32_t orow = (uint32_t)t_row * (uint32_t)a.H + (uint32_t)head;
-    uint16_t* out = (uint16_t*)a.out + (size_t)orow * D;
+    // Blocks db0 .. db0 + NDB - 1 of the row, and with db0 = 0 its normaliser.
+    auto store = [&](auto db0_t, auto ndb_t) {
+        constexpr int DB0 = decltype(db0_t)::value, NDB = decltype(ndb_t)::value;
+        if (!valid) return;
+        const float inv = empty ? 0.f : 1.0f / l_tot;
+        uint16_t* out = (uint16_t*)a.out + (size_t)orow * D;
 #pragma unroll
-    for (int db = 0; db < DB; ++db) {
+        for (int db = DB0; db < DB0 + NDB; ++db) {
 #pragma unroll
-        for (int jj = 0; jj < 4; ++jj) {
-            const int d0 = db * 32 + 8 * jj + 4 * hf;
-            const uint32_t lo = (uint32_t)f32_to_bf16_bits(o[db][4 * jj] * inv) |
-                                ((uint32_t)f32_to_bf16_bits(o[db][4 * jj + 1] * inv) << 16);
-            const uint32_t hi = (uint32_t)f32_to_bf16_bits(o[db][4 * jj + 2] * inv) |
-                                ((uint32_t)f32_to_bf16_bits(o[db][4 * jj + 3] * inv) << 16);
-            *(u32x2*)(out + d0) = u32x2{lo, hi};
+            for (int jj = 0; jj < 4; ++jj) {
+                const int d0 = db * 32 + 8 * jj + 4 * hf;
+                const uint32_t lo = (uint32_t)f32_to_bf16_bits(o[db][4 * jj] * inv) |
+                                    ((uint32_t)f32_to_bf16_bits(o[db][4 * jj + 1] * inv) << 16);
+                const uint32_t hi = (uint32_t)f32_to_bf16_bits(o[db][4 * jj + 2] * inv) |
+                                    ((uint32_t)f32_to_bf16_bits(o[db][4 * jj + 3] * inv) << 16);
+                *(u32x2*)(out + d0) = u32x2{lo, hi};
+            }
         }
+        if (DB0 == 0 && a.lse && hf == 0)
+            a.lse[orow] = empty ? -INFINITY : (m_run + __log2f(l_tot)) * kLn2;
+    };
+    if constexpr (KG == 1) {
+        leave();
+        store(Int<0>{}, Int<DB>{});
+    } else {
+        // The two key groups of a row group exchange halves of O (and m, l) through the
+        // ring's LDS (free: the last fills were waited for and read); each combines and
+        // stores one half of the row.
+        constexpr int HB = DB / 2, OW = HB * 16 * 64;      // blocks and floats of a half
+        static_assert(2 * RG * OW * 4 <= (int)sizeof(Kt) && RG * 1024 <= (int)sizeof(Vt), "exchange");
+        float* mine = (float*)&Kt[0][0] + (kg * RG + rg) * OW + lane;
+        const float* other = (const float*)&Kt[0][0] + ((1 - kg) * RG + rg) * OW + lane;
+        float* ml = (float*)&Vt[0][0] + rg * 256 + lane;
+        auto give = [&](auto db0_t) {
+            constexpr int DB0 = decltype(db0_t)::value;
+#pragma unroll
+            for (int db = 0; db < HB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mine[(db * 16 + v) * 64] = o[DB0 + db][v];
+            ml[kg * 128] = m_run;
+            ml[kg * 128 + 64] = l_tot;
+        };
+        auto take = [&](auto db0_t) {
+            constexpr int DB0 = decltype(db0_t)::value;
+            const float m1 = ml[(1 - kg) * 128], l1 = ml[(1 - kg) * 128 + 64];
+            const float m = fmaxf(m_run, m1);
+            const float w0 = m_run == -INFINITY ? 0.f : fast_exp2(m_run - m);
+            const float w1 = m1 == -INFINITY ? 0.f : fast_exp2(m1 - m);
+#pragma unroll
+            for (int db = 0; db < HB; ++db)
+#pragma unroll
+                for (int v = 0; v < 16; ++v)
+                    o[DB0 + db][v] = o[DB0 + db][v] * w0 + other[(db * 16 + v) * 64] * w1;
+            l_tot = l_tot * w0 + l1 * w1;
+            m_run = m;
+            store(db0_t, Int<HB>{});
+        };
+        __syncthreads();
+        if (kg == 0) give(Int<HB>{});
+        else give(Int<0>{});
+        __syncthreads();
+        if (kg == 0) take(Int<0>{});
+        else take(Int<HB>{});
     }
-    if (a.lse && hf == 0)
-        a.lse[orow] = empty ? -INFINITY : (m_run + __log2f(l_tot)) * kLn2;
 }
 
 
