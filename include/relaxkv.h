@@ -169,8 +169,9 @@ typedef struct relaxkv_problem {
  *                          edges[L+l] = sum_{p in R_l} (p+1), the full-prefix count.
  *   ctx      [L][T_c]      context lists of the construction variants (first |U| entries
  *                          of a row, ascending): row 0 for every layer (Global Sparse) or
- *                          row l for layer l (Layerwise Sparse); for the union and the
- *                          global target lists the set builds use it as scratch.
+ *                          row l for layer l (Layerwise Sparse).  relaxkv_build_sets and
+ *                          relaxkv_build_sets_global use its end as scratch (the
+ *                          latter never the target list it is given).
  *   g        [T_c]         float32 layer-mean scores of the last Global Sparse build.
  *   tiles    [2][L][H_kv+1] uint32 work counters of the bf16 attention, one slot per
  *                          context mode (0: the layer's context list, 1: Full-Prefix

@@ -519,25 +519,39 @@ constexpr int kCtxBitsMaxT = 1 << 18;                    // 64 KB of LDS; longer
 
 int set_blocks(const relaxkv_problem& p, int pb) { return (p.T_c + pb - 1) / pb; }
 
-template <bool GT>
+// Where the per-block counts go.  Anchor targets: the end of the context lists' array.
+// Global targets: its last row; the caller's list may be one of its rows (the
+// positions of a Global Sparse context repaired everywhere), so a list that overlaps
+// the last row moves them to the first, and with one layer to g (as large as a row).
 BlockScratch block_scratch(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk) {
+    const size_t per = (size_t)p.L * n_blk;
     BlockScratch sc;
-    const size_t per = GT ? n_blk : (size_t)p.L * n_blk;
-    // (the 16-bit counts take 2 T bytes, rounded up to whole words)
-    sc.n = s.ctx + (GT && n_blk > 1 ? ((size_t)p.T_c + 1) / 2 : 0);
+    sc.n = s.ctx + (size_t)p.L * p.T_c - (n_blk > 1 ? 3 : 1) * per;
     sc.e = sc.n + per;
     sc.f = sc.e + per;
-    sc.last = (int16_t*)s.ctx;
+    sc.last = nullptr;
+    return sc;
+}
+
+BlockScratch block_scratch_global(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk,
+                                  const int32_t* targets) {
+    const size_t T = (size_t)p.T_c;
+    int32_t* row = s.ctx + (size_t)(p.L - 1) * T;
+    if (targets < row + T && row < targets + T) row = p.L > 1 ? s.ctx : (int32_t*)s.g;
+    BlockScratch sc;
+    sc.last = (int16_t*)row;                             // 2 T bytes, rounded up to whole words
+    sc.n = row + (T + 1) / 2;
+    sc.e = sc.n + n_blk;
+    sc.f = sc.e + n_blk;
     return sc;
 }
 
 template <bool GT>
-void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, const int32_t* P,
-                   const int32_t* n_P, hipStream_t st) {
-    const int n_blk = set_blocks(p, pb);
-    hipLaunchKernelGGL(sets_blocks<GT>, dim3(n_blk), dim3(kSetThreads), pb * sizeof(int), st,
-                       s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, block_scratch<GT>(p, s, n_blk),
-                       s.tiles, (int)attn_tile_words(p));
+void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, const BlockScratch& sc,
+                   const int32_t* P, const int32_t* n_P, hipStream_t st) {
+    hipLaunchKernelGGL(sets_blocks<GT>, dim3(set_blocks(p, pb)), dim3(kSetThreads),
+                       pb * sizeof(int), st, s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, sc, s.tiles,
+                       (int)attn_tile_words(p));
 }
 
 }  // namespace
@@ -570,20 +584,21 @@ hipError_t launch_build_sets_global(const relaxkv_problem& p, const relaxkv_sets
                                     const int32_t* targets, const int32_t* n_targets,
                                     hipStream_t st) {
     const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    launch_blocks<true>(p, s, pb, targets, n_targets, st);
+    const BlockScratch sc = block_scratch_global(p, s, set_blocks(p, pb), targets);
+    launch_blocks<true>(p, s, pb, sc, targets, n_targets, st);
     hipLaunchKernelGGL(sets_emit_global, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
-                       dim3(kEmitThreads), pb * sizeof(int), st,
-                       block_scratch<true>(p, s, set_blocks(p, pb)), T, L, pb, targets, n_targets,
+                       dim3(kEmitThreads), pb * sizeof(int), st, sc, T, L, pb, targets, n_targets,
                        s.h, s.U, s.cidx, s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
     return hipGetLastError();
 }
 
 hipError_t launch_build_sets(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
     const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    launch_blocks<false>(p, s, pb, nullptr, nullptr, st);
+    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb));
+    launch_blocks<false>(p, s, pb, sc, nullptr, nullptr, st);
     hipLaunchKernelGGL(sets_emit, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
-                       dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb,
-                       block_scratch<false>(p, s, set_blocks(p, pb)), s.U, s.cidx, s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
+                       dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb, sc, s.U, s.cidx,
+                       s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
     return hipGetLastError();
 }
 

@@ -62,3 +62,25 @@ def test_context_limits(gpu_lib, T, construction):
     a = synthetic_scores(2, T, seed=T, levels=91)
     _, ref = build_both(case, a, construction)
     compare_context_sets(case, ref, construction)
+
+
+@pytest.mark.parametrize("L,T", [(1, 200), (1, 5000), (2, 300), (3, 9000)])
+@pytest.mark.parametrize("row", [0, -1])
+def test_targets_from_a_context_row(gpu_lib, L, T, row):
+    """A target list that is a row of the sets' own context lists: the build does
+    not use that row as scratch, so it gives the sets of a copy of the list, twice."""
+    case = Lists(L, T, 0.1)
+    a = torch.from_numpy(synthetic_scores(L, T, seed=T, levels=91)).cuda()
+    case.req.select(a, case.sets)
+    case.req.build_sets_context(a, relaxkv.CONTEXT_SETS_LAYERWISE, case.sets)
+    n = case.sets.counts[:1]
+    P = case.sets.ctx[row, :int(n)].cpu().numpy().astype(np.int64)
+    ref = oracle.build_sets_global(case.sets.anchors.cpu().numpy().astype(np.int64), T, P)
+    for _ in range(2):
+        case.req.build_sets_global(case.sets, case.sets.ctx[row], n)
+        got = case.got()
+        assert [r.tolist() for r in got["R"]] == [P.tolist()] * L
+        for l in range(L):
+            assert got["R_u"][l].tolist() == ref.R_u[l].tolist()
+            assert got["src"][l].tolist() == ref.src[l].tolist()
+            assert got["edges"][l] == int(ref.edges[l])
