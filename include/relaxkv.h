@@ -169,9 +169,9 @@ typedef struct relaxkv_problem {
  *                          edges[L+l] = sum_{p in R_l} (p+1), the full-prefix count.
  *   ctx      [L][T_c]      context lists of the construction variants (first |U| entries
  *                          of a row, ascending): row 0 for every layer (Global Sparse) or
- *                          row l for layer l (Layerwise Sparse).  relaxkv_build_sets and
- *                          relaxkv_build_sets_global use its end as scratch (the
- *                          latter never the target list it is given).
+ *                          row l for layer l (Layerwise Sparse); unused for the union, whose
+ *                          builds (relaxkv_build_sets, relaxkv_build_sets_global)
+ *                          leave it and g as they are.
  *   g        [T_c]         float32 layer-mean scores of the last Global Sparse build.
  *   tiles    [2][L][H_kv+1] uint32 work counters of the bf16 attention, one slot per
  *                          context mode (0: the layer's context list, 1: Full-Prefix

@@ -87,6 +87,26 @@ inline size_t attn_tile_words(const relaxkv_problem& p) {
     return 2 * (size_t)p.L * (size_t)(p.H_kv + 1);
 }
 
+// Positions per block of the set builds: the smallest power of two from 256 that
+// needs at most 64 blocks (the prefix over blocks is then one load per lane), up to
+// 16384 (its h fits 64 KB of LDS), which at T_c = 2^22 makes 256 blocks.
+constexpr int kMaxSetBlock = 16384;
+
+inline int set_block_positions(int T) {
+    int pb = 256;
+    while (pb < kMaxSetBlock && (T + pb - 1) / pb > 64) pb *= 2;
+    return pb;
+}
+
+// Words of the set builds' scratch, the 256-byte aligned array in front of
+// relaxkv_sets::tiles: n, e, f per layer and block for anchor targets; T_c int16
+// counts and n, e, f per block for a global target list (see sets.hip).
+inline size_t sets_scratch_words(int L, int T) {
+    const size_t n_blk = (size_t)((T + set_block_positions(T) - 1) / set_block_positions(T));
+    const size_t anchor = 3 * n_blk * (size_t)L, global = ((size_t)T + 1) / 2 + 3 * n_blk;
+    return anchor > global ? anchor : global;
+}
+
 // Rows an attention or cache-update launch may process for layer `layer`: the
 // caller's row capacity, and the bound on |R_l| of the lists the sets hold
 // (min(T_c, (L - l) k) for RelaxKV's targets: R_l lies in the union of S_l'

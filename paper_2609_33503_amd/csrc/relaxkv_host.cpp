@@ -24,7 +24,7 @@ bool dims_ok(const relaxkv_problem* p) {
 
 // Byte sizes of the set arrays, in carving order.
 struct SetsLayout {
-    size_t anchors, h, U, cidx, R_off, R_idx, R_u, src, rank, counts, edges, ctx, g, tiles, total;
+    size_t anchors, h, U, cidx, R_off, R_idx, R_u, src, rank, counts, edges, ctx, g, scratch, tiles, total;
 };
 
 SetsLayout sets_layout(const relaxkv_problem* p, int32_t k) {
@@ -43,9 +43,10 @@ SetsLayout sets_layout(const relaxkv_problem* p, int32_t k) {
     s.edges = align_up(2 * L * 8);
     s.ctx = align_up(L * T * 4);
     s.g = align_up(T * 4);
+    s.scratch = align_up(sets_scratch_words(p->L, p->T_c) * 4);
     s.tiles = align_up(attn_tile_words(*p) * 4);
     s.total = s.anchors + s.h + s.U + s.cidx + s.R_off + s.R_idx + s.R_u + s.src + s.rank + s.counts +
-              s.edges + s.ctx + s.g + s.tiles;
+              s.edges + s.ctx + s.g + s.scratch + s.tiles;
     return s;
 }
 
@@ -185,7 +186,7 @@ relaxkv_status relaxkv_sets_bind(const relaxkv_problem* p, void* dev_buf, size_t
     s.counts = (int32_t*)b; b += l.counts;
     s.edges = (int64_t*)b; b += l.edges;
     s.ctx = (int32_t*)b; b += l.ctx;
-    s.g = (float*)b; b += l.g;
+    s.g = (float*)b; b += l.g + l.scratch;      // (the scratch ends where tiles begins)
     s.tiles = (uint32_t*)b;
     s.global_targets = 0;
     s.context_sets = RELAXKV_CONTEXT_SETS_UNION;

@@ -39,15 +39,6 @@ constexpr int kSetThreads = 1024;
 constexpr int kEmitThreads = 256;              // one wave per layer
 constexpr int kEmitWaves = kEmitThreads / 64;
 
-// Positions per block: the smallest power of two from 256 that needs at most 64
-// blocks (the prefix over blocks is then one load per lane), up to 16384 (its h
-// fits 64 KB of LDS), which at T_c = 2^22 makes 256 blocks.
-int set_block_positions(int T) {
-    int pb = 256;
-    while (pb < 16384 && (T + pb - 1) / pb > 64) pb *= 2;
-    return pb;
-}
-
 // First index of the ascending list a[0..n) whose entry is >= v, searched by
 // groups of 16 lanes (16 probes a round, so 3 rounds for 4913 entries); every
 // lane of the wave calls, the lanes of a group with the same arguments.  For a
@@ -70,20 +61,22 @@ __device__ __forceinline__ int lower_bound16(const int32_t* __restrict__ a, int 
     return lo;
 }
 
-// Per-block counts the first launch leaves for the second, in the context lists'
-// array (unused until a construction variant fills it).  Anchor targets: n, e, f
+// Per-block counts the first launch leaves for the second, in the scratch array of
+// the sets buffer, which no caller is given (a caller may pass one of the sets' lists
+// as the targets, or keep using them after the build).  Anchor targets: n, e, f
 // of (layer, block) at [l * n_blk + b], with n = |R_l| in the block, e the sum of
 // the targets' 1-based union ranks within the block and f that of their 1-based
-// positions within it (each below 2^27).  Global targets: last[i], the number of
-// union positions of i's block up to i, minus one, and n, e, f of the block's
-// targets.  e and f are kept only for more than one block (then 3 L n_blk <= L T,
-// and 2 T + 12 n_blk <= 4 T bytes); a single block writes its sums itself.
+// positions within it.  Global targets: last[i], the number of union positions of i's
+// block up to i, minus one, and n, e, f of the block's targets.  e and f are kept
+// only for more than one block; a single block writes its sums itself.
 struct BlockScratch {
     int32_t* n;
     int32_t* e;
     int32_t* f;
     int16_t* last;
 };
+static_assert((long)kMaxSetBlock * (kMaxSetBlock + 1) / 2 <= INT32_MAX && kMaxSetBlock - 1 <= INT16_MAX,
+              "a block's e and f fit 32 bits, its counts 16");
 
 // One workgroup per block of positions: h of the block and the counts above (GT:
 // of the targets P instead of R_l; h is written by the second launch).  Also
@@ -519,30 +512,14 @@ constexpr int kCtxBitsMaxT = 1 << 18;                    // 64 KB of LDS; longer
 
 int set_blocks(const relaxkv_problem& p, int pb) { return (p.T_c + pb - 1) / pb; }
 
-// Where the per-block counts go.  Anchor targets: the end of the context lists' array.
-// Global targets: its last row; the caller's list may be one of its rows (the
-// positions of a Global Sparse context repaired everywhere), so a list that overlaps
-// the last row moves them to the first, and with one layer to g (as large as a row).
-BlockScratch block_scratch(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk) {
-    const size_t per = (size_t)p.L * n_blk;
+BlockScratch block_scratch(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk, bool global) {
+    const size_t words = sets_scratch_words(p.L, p.T_c), per = global ? n_blk : (size_t)p.L * n_blk;
+    int32_t* base = (int32_t*)s.tiles - (words * 4 + 255) / 256 * 64;
     BlockScratch sc;
-    sc.n = s.ctx + (size_t)p.L * p.T_c - (n_blk > 1 ? 3 : 1) * per;
+    sc.last = (int16_t*)base;                            // 2 T bytes, rounded up to whole words
+    sc.n = base + (global ? ((size_t)p.T_c + 1) / 2 : 0);
     sc.e = sc.n + per;
     sc.f = sc.e + per;
-    sc.last = nullptr;
-    return sc;
-}
-
-BlockScratch block_scratch_global(const relaxkv_problem& p, const relaxkv_sets& s, int n_blk,
-                                  const int32_t* targets) {
-    const size_t T = (size_t)p.T_c;
-    int32_t* row = s.ctx + (size_t)(p.L - 1) * T;
-    if (targets < row + T && row < targets + T) row = p.L > 1 ? s.ctx : (int32_t*)s.g;
-    BlockScratch sc;
-    sc.last = (int16_t*)row;                             // 2 T bytes, rounded up to whole words
-    sc.n = row + (T + 1) / 2;
-    sc.e = sc.n + n_blk;
-    sc.f = sc.e + n_blk;
     return sc;
 }
 
@@ -584,7 +561,7 @@ hipError_t launch_build_sets_global(const relaxkv_problem& p, const relaxkv_sets
                                     const int32_t* targets, const int32_t* n_targets,
                                     hipStream_t st) {
     const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    const BlockScratch sc = block_scratch_global(p, s, set_blocks(p, pb), targets);
+    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb), true);
     launch_blocks<true>(p, s, pb, sc, targets, n_targets, st);
     hipLaunchKernelGGL(sets_emit_global, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
                        dim3(kEmitThreads), pb * sizeof(int), st, sc, T, L, pb, targets, n_targets,
@@ -594,7 +571,7 @@ hipError_t launch_build_sets_global(const relaxkv_problem& p, const relaxkv_sets
 
 hipError_t launch_build_sets(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
     const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb));
+    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb), false);
     launch_blocks<false>(p, s, pb, sc, nullptr, nullptr, st);
     hipLaunchKernelGGL(sets_emit, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
                        dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb, sc, s.U, s.cidx,

@@ -192,6 +192,24 @@ def test_sets_bind_carves_buffer(rk):
     assert lib.relaxkv_sets_bind(ctypes.byref(p), None, nbytes, ctypes.byref(s)) == rk.EINVAL
 
 
+@pytest.mark.parametrize("L,T", [(1, 1), (1, 256), (1, 257), (1024, 256), (1024, 257), (3, 16385),
+                                 (1024, 70000), (1, (1 << 20) + 1), (2, 1 << 22), (511, 1 << 22)])
+def test_sets_scratch_between_g_and_tiles(rk, L, T):
+    """The builds' per-block counts lie between g and tiles, in no array of the
+    descriptor: 3 words per layer and block for the layer-wise targets; 2 bytes
+    per position and 3 words per block for a global list."""
+    lib = rk.load()
+    p = _problem(rk, L=L, T_c=T, n_query=1, H=1, H_kv=1, d=64)
+    s = _bound_sets(rk, p)
+    blk = 256
+    while blk < 16384 and -(-T // blk) > 64:
+        blk *= 2
+    n_blk = -(-T // blk)
+    assert n_blk <= 256
+    words = max(3 * L * n_blk, (T + 1) // 2 + 3 * n_blk)
+    assert s.tiles - (s.g + 4 * T) >= 4 * words
+
+
 def _bound_sets(rk, p):
     lib = rk.load()
     s = rk.Sets()
