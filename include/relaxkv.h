@@ -332,6 +332,9 @@ relaxkv_status relaxkv_select_global(const relaxkv_problem* p, const float* scor
  * relaxkv_build_sets.
  *   targets    device [T_c] int32: P, strictly ascending positions in [0, T_c).
  *   n_targets  device [1] int32: |P| in [0, T_c].
+ * Both may lie in the arrays of s (a row of ctx; U with counts[0]); one in an array
+ * that this call writes is read after U, cidx, R_off and counts are those of the
+ * anchors' union.
  * A list that is not strictly ascending within [0, T_c), or a count outside
  * [0, T_c], sets bit 1 of the error word (relaxkv_counts_to_host then returns
  * RELAXKV_EINVAL); the arrays are then unspecified but every index in them is

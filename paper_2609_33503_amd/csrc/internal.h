@@ -100,10 +100,11 @@ inline int set_block_positions(int T) {
 
 // Words of the set builds' scratch, the 256-byte aligned array in front of
 // relaxkv_sets::tiles: n, e, f per layer and block for anchor targets; T_c int16
-// counts and n, e, f per block for a global target list (see sets.hip).
+// counts and n, e, f per block for a global target list, and room for a copy of
+// the list and its length (see sets.hip).
 inline size_t sets_scratch_words(int L, int T) {
     const size_t n_blk = (size_t)((T + set_block_positions(T) - 1) / set_block_positions(T));
-    const size_t anchor = 3 * n_blk * (size_t)L, global = ((size_t)T + 1) / 2 + 3 * n_blk;
+    const size_t anchor = 3 * n_blk * (size_t)L, global = ((size_t)T + 1) / 2 + 3 * n_blk + T + 1;
     return anchor > global ? anchor : global;
 }
 

@@ -218,7 +218,9 @@ __device__ __forceinline__ void block_edges(const int32_t* n, const int32_t* e, 
 }
 
 // One wave per (block, layer): the block's part of U, cidx (layer 0's wave), R_l,
-// its compact indices, the source map, the rank map and the edge counts.
+// its compact indices, the source map, the rank map and the edge counts; without
+// LISTS only U, cidx, R_off and the counts.
+template <bool LISTS>
 __global__ __launch_bounds__(kEmitThreads) void sets_emit(
     const int32_t* __restrict__ h, int T, int L, int pb, BlockScratch sc,
     int32_t* __restrict__ U, int32_t* __restrict__ cidx, int32_t* __restrict__ R_off,
@@ -262,6 +264,7 @@ __global__ __launch_bounds__(kEmitThreads) void sets_emit(
         if (l == 0) counts[0] = tot;                     // R_0 = U
         if (l == L - 1) R_off[L] = off + tot;
     }
+    if (!LISTS && l > 0) return;
     int32_t* src_l = src + (size_t)l * T;
     int32_t* rank_l = rank + (size_t)l * T;
     int u = u_base, r = pre;
@@ -280,9 +283,9 @@ __global__ __launch_bounds__(kEmitThreads) void sets_emit(
             const bool in = hv[x] >= 0, act = hv[x] >= l;    // (l >= 0, so act implies in)
             const uint64_t mu = __ballot(in), ma = __ballot(act);
             const int uc = u + lanes_below(mu), rc = r + lanes_below(ma);
-            if (i < T) rank_l[i] = act ? rc : -1;
-            if (in) src_l[uc] = act ? rc : -1;
-            if (act) {
+            if (LISTS && i < T) rank_l[i] = act ? rc : -1;
+            if (LISTS && in) src_l[uc] = act ? rc : -1;
+            if (LISTS && act) {
                 R_idx[off + rc] = i;
                 R_u[off + rc] = uc;
                 e_sum += uc + 1;                         // |C_l(p)| = compact index of p + 1
@@ -296,7 +299,7 @@ __global__ __launch_bounds__(kEmitThreads) void sets_emit(
             r += __popcll(ma);
         }
     }
-    if (b > 0) return;
+    if (!LISTS || b > 0) return;
     if (n_blk > 1) {
         const size_t at = (size_t)l * n_blk;
         block_edges(cnt + at, sc.e + at, sc.f + at, n_blk, pb, [&](int j) { return cnt[j]; }, e_sum, ef_sum);
@@ -409,6 +412,13 @@ __global__ __launch_bounds__(kEmitThreads) void sets_emit_global(
             h[b0 + i] = t >= 0 ? L - 1 : -1;
         }
     }
+}
+
+// A copy of the target list and its length.
+__global__ void sets_copy_list(const int32_t* P, const int32_t* n_P, int T, int32_t* to, int32_t* n_to) {
+    const int n = n_P[0], i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < min(max(n, 0), T)) to[i] = P[i];
+    if (i == 0) n_to[0] = n;
 }
 
 // ------------------------------------------------ context-construction variants
@@ -531,6 +541,29 @@ void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, cons
                        (int)attn_tile_words(p));
 }
 
+// The anchors' union and targets; without LISTS only U, cidx, R_off and the counts.
+template <bool LISTS>
+void launch_anchor_sets(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
+    const int T = p.T_c, L = p.L, pb = set_block_positions(T), n_blk = set_blocks(p, pb);
+    const BlockScratch sc = block_scratch(p, s, n_blk, false);
+    launch_blocks<false>(p, s, pb, sc, nullptr, nullptr, st);
+    hipLaunchKernelGGL(sets_emit<LISTS>, dim3(n_blk, (L + kEmitWaves - 1) / kEmitWaves),
+                       dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb, sc, s.U, s.cidx,
+                       s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
+}
+
+// Whether the n words at a overlap an array that a build of target lists writes.
+bool in_outputs(const relaxkv_problem& p, const relaxkv_sets& s, const int32_t* a, size_t n) {
+    const size_t L = p.L, T = p.T_c;
+    const struct { const void* at; size_t words; } outs[] = {
+        {s.h, T}, {s.U, T}, {s.cidx, T}, {s.R_off, L + 1}, {s.R_idx, L * T}, {s.R_u, L * T},
+        {s.src, L * T}, {s.rank, L * T}, {s.counts, L + 2}, {s.edges, 4 * L}};
+    const uintptr_t a0 = (uintptr_t)a;
+    for (const auto& o : outs)
+        if (a0 < (uintptr_t)o.at + 4 * o.words && (uintptr_t)o.at < a0 + 4 * n) return true;
+    return false;
+}
+
 }  // namespace
 
 hipError_t launch_build_sets_context(const relaxkv_problem& p, const float* scores,
@@ -560,22 +593,28 @@ hipError_t launch_build_sets_context(const relaxkv_problem& p, const float* scor
 hipError_t launch_build_sets_global(const relaxkv_problem& p, const relaxkv_sets& s,
                                     const int32_t* targets, const int32_t* n_targets,
                                     hipStream_t st) {
-    const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb), true);
+    const int T = p.T_c, L = p.L, pb = set_block_positions(T), n_blk = set_blocks(p, pb);
+    const BlockScratch sc = block_scratch(p, s, n_blk, true);
+    // A list (or its length) in an array that this build writes, for instance U with
+    // counts[0], stands for what the array holds once the union is rebuilt from the
+    // anchors: the union comes first, and the build then reads a copy of the list.
+    if (in_outputs(p, s, targets, T) || in_outputs(p, s, n_targets, 1)) {
+        launch_anchor_sets<false>(p, s, st);
+        int32_t* copy = sc.f + n_blk;
+        hipLaunchKernelGGL(sets_copy_list, dim3((T + 255) / 256), dim3(256), 0, st, targets, n_targets,
+                           T, copy, copy + T);
+        targets = copy;
+        n_targets = copy + T;
+    }
     launch_blocks<true>(p, s, pb, sc, targets, n_targets, st);
-    hipLaunchKernelGGL(sets_emit_global, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
+    hipLaunchKernelGGL(sets_emit_global, dim3(n_blk, (L + kEmitWaves - 1) / kEmitWaves),
                        dim3(kEmitThreads), pb * sizeof(int), st, sc, T, L, pb, targets, n_targets,
                        s.h, s.U, s.cidx, s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
     return hipGetLastError();
 }
 
 hipError_t launch_build_sets(const relaxkv_problem& p, const relaxkv_sets& s, hipStream_t st) {
-    const int T = p.T_c, L = p.L, pb = set_block_positions(T);
-    const BlockScratch sc = block_scratch(p, s, set_blocks(p, pb), false);
-    launch_blocks<false>(p, s, pb, sc, nullptr, nullptr, st);
-    hipLaunchKernelGGL(sets_emit, dim3(set_blocks(p, pb), (L + kEmitWaves - 1) / kEmitWaves),
-                       dim3(kEmitThreads), 0, st, (const int32_t*)s.h, T, L, pb, sc, s.U, s.cidx,
-                       s.R_off, s.R_idx, s.R_u, s.src, s.rank, s.counts, s.edges);
+    launch_anchor_sets<true>(p, s, st);
     return hipGetLastError();
 }
 

@@ -43,3 +43,32 @@ def test_union_builds_leave_the_context_lists(gpu_lib, L, T):
         check(sets.ctx[l], n_u)
     if L > 1:                                          # a list that begins inside a row
         check(sets.ctx.view(-1)[5:5 + T], n_u - 5)
+
+
+@pytest.mark.parametrize("L,T", [(1, 200), (2, 700), (3, 9000)])
+def test_targets_in_an_array_the_build_writes(gpu_lib, L, T):
+    """The union list as the target list, right after a new selection (U and its
+    count still those of the old anchors): the build rebuilds the union first.  R_0
+    in R_idx, with its count, is the same list."""
+    case = Lists(L, T, 0.1)
+    sets = case.sets
+    for seed in (1, 2):                                # the second time U is a stale list
+        a = synthetic_scores(L, T, seed=seed, levels=91)
+        anchors = oracle.select(a.astype(np.float64), case.k)
+        case.req.select(torch.from_numpy(a).cuda(), sets)
+        if seed == 1:
+            case.req.build_sets(sets)
+    U = oracle.build_sets(anchors, T).U
+    ref = oracle.build_sets_global(anchors, T, U)
+    case.req.build_sets_global(sets, sets.U, sets.counts[:1])
+    compare_global_sets(case.got(), ref)
+    case.req.build_sets(sets)
+    case.req.build_sets_global(sets, sets.R_idx[:T], sets.counts[1:2])
+    compare_global_sets(case.got(), ref)
+    # a count from the sets, a list from elsewhere, and the other way round
+    P = torch.zeros(T, dtype=torch.int32, device="cuda")
+    P[:len(U)] = torch.from_numpy(np.asarray(U, dtype=np.int32)).cuda()
+    case.req.build_sets_global(sets, P, sets.counts[:1])
+    compare_global_sets(case.got(), ref)
+    case.req.build_sets_global(sets, sets.U, torch.tensor([3], dtype=torch.int32, device="cuda"))
+    compare_global_sets(case.got(), oracle.build_sets_global(anchors, T, U[:3]))

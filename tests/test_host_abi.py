@@ -197,7 +197,7 @@ def test_sets_bind_carves_buffer(rk):
 def test_sets_scratch_between_g_and_tiles(rk, L, T):
     """The builds' per-block counts lie between g and tiles, in no array of the
     descriptor: 3 words per layer and block for the layer-wise targets; 2 bytes
-    per position and 3 words per block for a global list."""
+    per position and 3 words per block for a global list, and a copy of the list."""
     lib = rk.load()
     p = _problem(rk, L=L, T_c=T, n_query=1, H=1, H_kv=1, d=64)
     s = _bound_sets(rk, p)
@@ -206,7 +206,7 @@ def test_sets_scratch_between_g_and_tiles(rk, L, T):
         blk *= 2
     n_blk = -(-T // blk)
     assert n_blk <= 256
-    words = max(3 * L * n_blk, (T + 1) // 2 + 3 * n_blk)
+    words = max(3 * L * n_blk, (T + 1) // 2 + 3 * n_blk + T + 1)
     assert s.tiles - (s.g + 4 * T) >= 4 * words
 
 
