@@ -571,7 +571,7 @@ __global__ __launch_bounds__(MfmaF32<R>::waves * 64) void attn_f32(AttnArgs a) {
     const int t = (int)((valid ? row : last) / a.G);
     const int head = g * a.G + (int)((valid ? row : last) - (long)t * a.G);
     const int n_keys = max(lim_of[last / a.G], 0) + 1;   // limits ascend with the row
-    const size_t orow = (size_t)t * a.H + head;
+    const uint32_t orow = (uint32_t)t * (uint32_t)a.H + (uint32_t)head;   // below T_c * H <= 2^32
     auto id_of = [&](int c) {
         const int r = FULL ? a.rank_l[c] : a.src_l[c];
         return r >= 0 ? r : ~(FULL ? c : a.U[c]);
@@ -579,8 +579,8 @@ __global__ __launch_bounds__(MfmaF32<R>::waves * 64) void attn_f32(AttnArgs a) {
     attn_f32_rows<D, R>(
         *(AttnF32Lds<D, R>*)f32_lds, (const float*)a.k_new + g * D, (const float*)a.v_new + g * D,
         (int64_t)a.Hkv * D, (const float*)a.kc + g * a.kv_sh, (const float*)a.vc + g * a.kv_sh, a.kv_st,
-        id_of, n_keys, (const float*)a.q_new + orow * D, lim_of[t], a.scale, valid,
-        (float*)a.out + orow * D, a.lse ? a.lse + orow : nullptr);
+        id_of, n_keys, (const float*)a.q_new + (size_t)orow * D, lim_of[t], a.scale, valid,
+        (float*)a.out, a.lse, orow);
 }
 
 constexpr int kNW = RELAXKV_ATTN_WAVES;

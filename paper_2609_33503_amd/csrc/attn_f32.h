@@ -22,7 +22,10 @@
 // that read 64 K rows side by side.  Per launch, before and now: 2.5K context, 1100
 // targets, 32q/8kv heads, d 128: 1522 -> 148 us (47 TFLOP/s); 64 query tokens over
 // it 900 -> 80 us; 16 query tokens over 1K keys, 4q/2kv heads, d 64: 154 -> 20 us
-// (four workgroups, so latency: 37 us as 32-row tiles of 8 waves).
+// (four workgroups, so latency: 37 us as 32-row tiles of 8 waves).  With all V loads
+// of half a block ahead of its products, as the test for non-finite V needs them:
+// 75 -> 68 us for the 64 query tokens, 700 targets' full prefix there 262 -> 221 us,
+// the 16-row launches within 2% (d 64) or 7% faster (d 128).
 #pragma once
 
 #include <math.h>
@@ -39,6 +42,20 @@ typedef float f32x2_u __attribute__((ext_vector_type(2), aligned(4)));
 // work per workgroup, 16 waves); larger ones take 32 rows, which read K and V half
 // as often.
 inline bool attn_f32_small(long rows, int Hkv) { return (rows + 15) / 16 * Hkv <= 256; }
+
+// Inf or NaN, from the bits, which are hidden from the compiler: the files of these
+// kernels are built without NaN semantics, so it would fold a test for NaN away.
+__device__ __forceinline__ bool not_finite(float x) {
+    uint32_t u = __float_as_uint(x);
+    asm("" : "+v"(u));
+    return (u & 0x7fffffffu) >= 0x7f800000u;
+}
+
+// The bits of z + 0 * x: 0 while every x is finite, a NaN's afterwards.
+__device__ __forceinline__ uint32_t zero_or_nan(float x, uint32_t z) {
+    asm("v_fmac_f32_e32 %0, 0, %1" : "+v"(z) : "v"(x));
+    return z;
+}
 
 template <int R> struct MfmaF32;
 template <> struct MfmaF32<32> {
@@ -69,14 +86,15 @@ struct AttnF32Lds {
 // fs) when >= 0, else the cached position ~id of kc/vc (row stride cs); all four
 // point at the KV head's first element.  q_row: the lane's query row; lim: its last
 // visible key, -1 for none (the row is then the empty sum: O = 0, lse = -inf).
-// n_keys > every row's limit.  out_row/lse_out: the lane's row (lse_out may be
-// null); written only if `valid`.
+// A row's result depends on no K or V it does not see, not even on a NaN there.
+// n_keys > every row's limit.  The lane's row is row orow of out [][D] and lse_out
+// (may be null); written only if `valid`.
 template <int D, int R, typename IdOf>
 __device__ __forceinline__ void attn_f32_rows(AttnF32Lds<D, R>& sm, const float* kn,
                                               const float* vn, int64_t fs, const float* kc,
                                               const float* vc, int64_t cs, IdOf id_of, int n_keys,
                                               const float* q_row, int lim, float scale, bool valid,
-                                              float* out_row, float* lse_out) {
+                                              float* out, float* lse_out, uint32_t orow) {
     typedef MfmaF32<R> M32;
     typedef typename M32::Acc Acc;
     constexpr int NW = M32::waves, NG = 64 / R, NV = sizeof(Acc) / 4;
@@ -97,6 +115,29 @@ __device__ __forceinline__ void attn_f32_rows(AttnF32Lds<D, R>& sm, const float*
         const float* kp = (id >= 0 ? kn + id * fs : kc + ~id * cs) + 4 * grp;
 #pragma unroll
         for (int j = 0; j < J; ++j) kf[j] = *(const f32x4_u*)(kp + 4 * NG * j);
+    };
+    // What is not finite in a block's V, added to the rows that see its key (rare; the
+    // wave's part of the output area holds P meanwhile).
+    auto add_odd = [&](const Acc& p, int id, int ex) {
+#pragma unroll
+        for (int v = 0; v < NV; ++v) sm.o[w][key_of(v)][rl] = p[v];
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll 1
+        for (int kk = 0; kk < R; ++kk) {
+            const int vid = __shfl(id, kk, 64);
+            const float* vp = vid >= 0 ? vn + vid * fs : vc + ~vid * cs;
+            const float pk = sm.o[w][kk][rl];
+#pragma unroll
+            for (int v = 0; v < NV; ++v) {
+#pragma unroll
+                for (int db = 0; db < DB; ++db) {
+                    const float x = vp[DB * key_of(v) + db];
+                    if (kk <= ex && not_finite(x)) o[db][v] = fmaf(pk, x, o[db][v]);
+                }
+                __builtin_amdgcn_sched_barrier(0);       // (few loads live at once)
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
     };
     int b = w, id = 0;
     if (b * R < n_keys) {
@@ -138,28 +179,54 @@ __device__ __forceinline__ void attn_f32_rows(AttnF32Lds<D, R>& sm, const float*
             s[v] = expf(s[v] - m_ref);
             l_run += s[v];
         }
+        // O^T += V^T P^T, at d 128 half of the V rows at a time (for the registers).  A
+        // masked key's probability is 0, but 0 * Inf is no number: in a block with a
+        // masked key, what is not finite in V (found by one multiply-add per value) is
+        // left out of the product, and the rows that see it get it afterwards.
+        constexpr int NH = D / 64, VH = NV / NH;
+        const bool masked = __any(ex < R - 1);
+        bool odd = false;
 #pragma unroll
-        for (int v = 0; v < NV; ++v) {
-            // (at d 128 half of the V rows at a time, for the registers)
-            if (D == 128 && v == NV / 2) __builtin_amdgcn_sched_barrier(0);
-            const int vid = __shfl(id, key_of(v), 64);
-            const float* vp = (vid >= 0 ? vn + vid * fs : vc + ~vid * cs) + DB * rl;
-            float vv[DB];
-            if constexpr (DB == 2) {
-                const f32x2_u x = *(const f32x2_u*)vp;
-                vv[0] = x[0];
-                vv[1] = x[1];
-            } else {
+        for (int h = 0; h < NH; ++h) {
+            if (h) __builtin_amdgcn_sched_barrier(0);
+            float vv[VH][DB];
 #pragma unroll
-                for (int q = 0; q < DB / 4; ++q) {
-                    const f32x4 x = *(const f32x4_u*)(vp + 4 * q);
+            for (int v = 0; v < VH; ++v) {
+                const int vid = __shfl(id, key_of(h * VH + v), 64);
+                const float* vp = (vid >= 0 ? vn + vid * fs : vc + ~vid * cs) + DB * rl;
+                if constexpr (DB == 2) {
+                    const f32x2_u x = *(const f32x2_u*)vp;
+                    vv[v][0] = x[0];
+                    vv[v][1] = x[1];
+                } else {
 #pragma unroll
-                    for (int i = 0; i < 4; ++i) vv[4 * q + i] = x[i];
+                    for (int q = 0; q < DB / 4; ++q) {
+                        const f32x4 x = *(const f32x4_u*)(vp + 4 * q);
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) vv[v][4 * q + i] = x[i];
+                    }
+                }
+            }
+            if (masked) {
+                uint32_t z = 0;
+#pragma unroll
+                for (int v = 0; v < VH; ++v)
+#pragma unroll
+                    for (int db = 0; db < DB; ++db) z = zero_or_nan(vv[v][db], z);
+                if (__any(z != 0)) {
+                    odd = true;
+#pragma unroll
+                    for (int v = 0; v < VH; ++v)
+#pragma unroll
+                        for (int db = 0; db < DB; ++db) vv[v][db] = not_finite(vv[v][db]) ? 0.f : vv[v][db];
                 }
             }
 #pragma unroll
-            for (int db = 0; db < DB; ++db) o[db] = M32::mac(vv[db], s[v], o[db]);
+            for (int v = 0; v < VH; ++v)
+#pragma unroll
+                for (int db = 0; db < DB; ++db) o[db] = M32::mac(vv[v][db], s[h * VH + v], o[db]);
         }
+        if (odd) add_odd(s, id, ex);
         id = id_n;
         b = bn;
     }
@@ -187,6 +254,7 @@ __device__ __forceinline__ void attn_f32_rows(AttnF32Lds<D, R>& sm, const float*
     const float inv = lim < 0 ? 0.f : 1.0f / z;
     constexpr int PER = D * R / (64 * NW);               // d values a thread writes
     const int d0 = tid / R * PER;
+    float* out_row = out + (size_t)orow * D;
 #pragma unroll
     for (int e = 0; e < PER; ++e) {
         float acc = 0.f;
@@ -194,7 +262,7 @@ __device__ __forceinline__ void attn_f32_rows(AttnF32Lds<D, R>& sm, const float*
         for (int ww = 0; ww < NW; ++ww) acc += wt[ww] * sm.o[ww][d0 + e][rl];
         out_row[d0 + e] = acc * inv;
     }
-    if (lse_out && tid < R) *lse_out = lim < 0 ? -INFINITY : M + logf(z);
+    if (lse_out && tid < R) lse_out[orow] = lim < 0 ? -INFINITY : M + logf(z);
 }
 
 }  // namespace relaxkv

@@ -509,11 +509,11 @@ __global__ __launch_bounds__(MfmaF32<R>::waves * 64) void qattn_f32(
     const bool valid = row0 < n_rows;
     const int row = valid ? row0 : last;
     const int t = row / G, h = g * G + row - t * G;
-    const size_t orow = (size_t)t * H + h;
+    const uint32_t orow = (uint32_t)t * H + h;
     auto id_of = [&](int c) { return c < T ? ~c : c - T; };
     attn_f32_rows<D, R>(*(AttnF32Lds<D, R>*)f32_lds, kq + g * D, vq + g * D, (int64_t)Hkv * D,
                         kc + g * ks.head, vc + g * ks.head, ks.token, id_of, T + last / G + 1,
-                        q + orow * D, T + t, scale, valid, out + orow * D, lse ? lse + orow : nullptr);
+                        q + (size_t)orow * D, T + t, scale, valid, out, lse, orow);
 }
 
 int qa_waves(int rows_pad) {
