@@ -2,6 +2,8 @@
 the full checks refuse, and tensors it does not take (subclasses, other strides of
 size-1 dimensions) still pass through the full checks."""
 
+import copy
+
 import pytest
 import torch
 
@@ -60,3 +62,26 @@ def test_binding_checks(gpu_lib):
     with pytest.raises(ValueError):
         req.update_cache(sets, 0, r[1], r[2][:-1], k, k)
     torch.cuda.synchronize()
+
+
+def test_calls_use_the_request_s_descriptor(gpu_lib):
+    """A request whose descriptor is replaced (a copy with another softmax scale)
+    runs with the new one, and the request it was copied from with its own."""
+    L, Qn, H, Hkv, T, d = 2, 3, 4, 2, 70, 64
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    q, k = torch.randn(L, Qn, H, d, **bf), torch.randn(L, Hkv, T, d, **bf)
+    kq = torch.randn(Qn, Hkv, d, **bf)
+
+    def results(req):
+        a, out = torch.empty(L, T, device="cuda"), torch.empty(Qn, H, d, **bf)
+        req.score(req.alloc_workspace(), a)
+        req.query_attn(1, k, k, kq, kq, out, ws=req.alloc_query_workspace())
+        return a, out
+    req = relaxkv.Request(q, k, k, 0.2)
+    other = copy.copy(req)
+    other.p = relaxkv.Problem.from_buffer_copy(req.p)
+    other.p.softmax_scale = 0.5
+    want = [results(relaxkv.Request(q, k, k, 0.2, softmax_scale=s)) for s in (0.0, 0.5)]
+    for got, ref in zip((results(req), results(other)), want):
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
+    assert not torch.equal(want[0][1], want[1][1])
