@@ -557,10 +557,10 @@ __global__ __launch_bounds__(MfmaF32<R>::waves * 64) void attn_f32(AttnArgs a) {
     extern __shared__ __attribute__((aligned(16))) char f32_lds[];
     const int nR_dev = a.counts[1 + a.layer];
     const int nR = min(nR_dev, a.cap);
-    if (nR_dev > a.cap && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0)
+    if (nR_dev > a.cap && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0)
         atomicOr(a.err, RELAXKV_ERR_ROWS);
     const long nrows = (long)nR * a.G;
-    const long tile = (nrows + R - 1) / R - 1 - blockIdx.x;
+    const long tile = (nrows + R - 1) / R - 1 - ((long)blockIdx.z * gridDim.x + blockIdx.x);
     if (tile < 0) return;
     const int g = blockIdx.y;
     const long row = tile * R + threadIdx.x % R;
@@ -622,8 +622,11 @@ void launch_one(const AttnArgs& a, bool bf16, int n_bound, hipStream_t st) {
     } else {
         const long rows = (long)n_bound * a.G;
         auto go = [&](auto kernel, int r, int waves, size_t lds) {
-            hipLaunchKernelGGL(kernel, dim3((unsigned)((rows + r - 1) / r), a.Hkv), dim3(waves * 64), lds,
-                               st, a);
+            // A grid dimension times its threads stays below 2^32: 2^22 workgroups of at
+            // most 512 threads in x (R = 32), the rest (up to 2^32 rows) in z.
+            const long tiles = (rows + r - 1) / r, nx = tiles < (1L << 22) ? tiles : 1L << 22;
+            hipLaunchKernelGGL(kernel, dim3((unsigned)nx, a.Hkv, (unsigned)((tiles + nx - 1) / nx)),
+                               dim3(waves * 64), lds, st, a);
         };
         if (attn_f32_small(rows, a.Hkv))
             go(attn_f32<D, FULL, 16>, 16, MfmaF32<16>::waves, sizeof(AttnF32Lds<D, 16>));
