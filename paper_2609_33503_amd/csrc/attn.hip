@@ -589,20 +589,26 @@ constexpr int kNW2 = 8;                    // waves of the two-key-group kernel
 constexpr int kAttnRows2 = kNW2 / 2 * 32;  // its rows per workgroup
 
 // Key groups of a launch of `rows` (target, head) rows per KV head, by its count of
-// 384-row tiles: two up to 5/4 of the chip's 256 CUs at d 128, up to three times
-// them at d 64 (whose smaller workgroups fit a CU twice), one past that.  While
-// every tile has a CU to itself the launch lasts as long as the longest tile's
-// steps, so a third of the rows and half of the steps per workgroup is shorter;
-// past it the extra fills per row count.  Measured in us, one against two key
-// groups, 8 KV heads: d 128: 24 tiles (1.5K context) 28.4 / 17.8, 104 (8K) 163 / 82,
-// 264 (8K) 173 / 152, 264 (16K) 341 / 289, 312 (8K) 181 / 174, 328 (9K) 199 / 200,
-// 352 (8K) 186 / 199, 552 (16K) 493 / 576; d 64: 104 (8K) 118 / 59, 264 (8K) 128 /
-// 92, 408 (8K) 138 / 126, 568 (16K) 318 / 311, 752 (16K) 419 / 407, 1400 (32K)
-// 1420 / 1466.
+// 384-row tiles: two up to 5/4 of the chip's 256 CUs at d 128, up to 432 tiles at
+// d 64 (whose smaller workgroups fit a CU twice) and there again from 600 to 768
+// tiles; one otherwise.  While every tile has a CU to itself the launch lasts as long
+// as the longest tile's steps, so a third of the rows and half of the steps per
+// workgroup is shorter; past it the extra fills per row count, and at d 64 from 433
+// to 600 tiles two rounds of the larger workgroups fit the chip about as well.
+// Measured in us, one against two key groups, 8 KV heads: d 128: 24 tiles (1.5K
+// context) 28.4 / 17.8, 104 (8K) 163 / 82, 264 (8K) 173 / 152, 264 (16K) 341 / 289, 312
+// (8K) 181 / 174, 328 (9K) 199 / 200, 352 (8K) 186 / 199, 552 (16K) 493 / 576; d 64: 104
+// (8K) 118 / 59, 264 (8K) 128 / 92, 592 (12K) 260 / 255, 624 (14K) 315 / 307, 752 (16K)
+// 419 / 407, 1400 (32K) 1420 / 1466.  d 64 at other KV-head counts: 364 (2 heads, 10K)
+// 156 / 136, 400 (1, 16K) 250 / 235, 416 (4, 16K) 250 / 241, 428 (4, 16K) 251 / 248, 440
+// (2, 12K) 193 / 191 and over the full prefix 297 / 300, 452 (2, 16K) 258 / 263, 512 (2,
+// 14K) 250 / 254, 539 (1, 24K) 428 / 449, 552 (2, 16K) 314 / 319, 598 (2, 16K) 343 / 339
+// and 536 / 536, 668 (2, 24K) 558 / 548.
 int attn_key_groups(long rows, int Hkv, int d) {
     constexpr long kCUs = 256;
     const long tiles = (rows + kAttnRows - 1) / kAttnRows * Hkv;
-    return tiles <= (d == 128 ? kCUs * 5 / 4 : kCUs * 3) ? 2 : 1;
+    if (d == 128) return tiles <= kCUs * 5 / 4 ? 2 : 1;
+    return tiles <= 432 || (tiles >= 600 && tiles <= 768) ? 2 : 1;
 }
 
 template <int D, bool FULL>

@@ -1,6 +1,6 @@
 """The bf16 attention on both sides of its key-group rule: launches of at most 320
-384-row tiles (768 at d 64) split each workgroup's keys over two wave groups, larger
-ones do not.  Sampled targets (the first ones, whose contexts end inside the first key
+384-row tiles (432, and 600 to 768, at d 64) split each workgroup's keys over two wave
+groups, others do not.  Sampled targets (the first ones, whose contexts end inside the first key
 group's keys, and the last of a ragged tile among them) against the oracle, and
 the work counters are zero afterwards on both sides."""
 
@@ -46,3 +46,9 @@ def test_key_groups(gpu_lib, T, G, H_kv, n, d):
         assert_close(got[~empty], O_ref[~empty], w, f"{mode} out", rel_gate=1e-2)
         assert_close(got_lse[~empty], lse_ref[~empty], w, f"{mode} lse")
         assert int(case.sets.tiles.abs().sum()) == 0
+
+
+# 13, 14, 18 and 19 tiles of 32 KV heads: 416 (two key groups), 448, 576, 608 (two)
+@pytest.mark.parametrize("n", [1248, 1249, 1728, 1729])
+def test_key_groups_d64_lines(gpu_lib, n):
+    test_key_groups(gpu_lib, 1800, 4, 32, n, 64)
