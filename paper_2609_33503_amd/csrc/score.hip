@@ -431,7 +431,7 @@ __global__ void score_merge(const float2* __restrict__ stats, int n_groups, int 
 // 4 (l / 32) (the contraction may take its index in any order, the same on both
 // sides).  Against the VALU kernels before (one thread per key and all rows, one
 // workgroup per row and all keys): 12 layers of 3000 keys, 64 query tokens, 32q/8kv
-// heads, d 128, 8.06 -> 0.53 ms; 2 layers of 1024 keys, 4q/2kv heads 44 -> 30 us.
+// heads, d 128, 8.06 -> 0.53 ms; 2 layers of 1024 keys, 4q/2kv heads 44 -> 23 us.
 constexpr int kF32Waves = 8;            // of the column sums
 constexpr int kF32StatsWaves = 16;
 
@@ -452,25 +452,30 @@ __device__ __forceinline__ f32x16 dot_f32(const f32x4 (&a)[D / 8], const f32x4 (
 }
 
 // Natural-log normalisers: a workgroup takes 32 (token, head) rows of a KV head of a
-// layer; its waves take the 32-key blocks in turn (S^T = K Q^T, one row per lane),
-// each with its own running (max, sum), merged in wave order.
+// layer and one of n_split splits of the keys (see f32_stats_split); its waves take the
+// 32-key blocks in turn (S^T = K Q^T, one row per lane), each with its own running
+// (max, sum), merged in wave order.  Of several splits it leaves its (max, sum), which
+// score_merge_f32 merges in split order.
 template <int D>
 __global__ __launch_bounds__(kF32StatsWaves * 64) void score_stats_f32(
     const float* __restrict__ q, const float* __restrict__ kc, KvStrides ks, int T, int Qn, int H,
-    int Hkv, int G, int n_rows, int rows_pad, float scale, float* __restrict__ lse_nat) {
+    int Hkv, int G, int n_rows, int rows_pad, int keys_per_split, int n_split, float scale,
+    float2* __restrict__ stats, float* __restrict__ lse_nat) {
     __shared__ float red_m[kF32StatsWaves][32], red_z[kF32StatsWaves][32];
     const int g = blockIdx.y, l = blockIdx.z;
+    const int rb = blockIdx.x / n_split, split = blockIdx.x - rb * n_split;
+    const int key1 = min(T, (split + 1) * keys_per_split);
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hf = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-    const int row = blockIdx.x * 32 + r32, rr = min(row, n_rows - 1);
+    const int row = rb * 32 + r32, rr = min(row, n_rows - 1);
     const float* Kg = kc + l * ks.layer + g * ks.head;
     f32x4 qf[D / 8], kf[D / 8];
     load_row_f32<D>(qf, q + (((size_t)l * Qn + rr / G) * H + g * G + rr % G) * D, hf);
     float m = -INFINITY, z = 0.f;
-    for (int k0 = w * 32; k0 < T; k0 += kF32StatsWaves * 32) {
+    for (int k0 = split * keys_per_split + w * 32; k0 < key1; k0 += kF32StatsWaves * 32) {
         load_row_f32<D>(kf, Kg + min(k0 + r32, T - 1) * ks.token, hf);
         f32x16 s = dot_f32<D>(kf, qf);
-        const int ex = T - 1 - k0 - 4 * hf;              // last key of the block
+        const int ex = key1 - 1 - k0 - 4 * hf;           // last key of the block
         float mx = m;
 #pragma unroll
         for (int v = 0; v < 16; ++v) {
@@ -496,8 +501,23 @@ __global__ __launch_bounds__(kF32StatsWaves * 64) void score_stats_f32(
         for (int i = 0; i < kF32StatsWaves; ++i) M = fmaxf(M, red_m[i][r32]);
         for (int i = 0; i < kF32StatsWaves; ++i)
             if (red_m[i][r32] != -INFINITY) Z += red_z[i][r32] * expf(red_m[i][r32] - M);
-        lse_nat[((size_t)l * Hkv + g) * rows_pad + row] = M + logf(Z);
+        const size_t lg = (size_t)l * Hkv + g;
+        if (n_split == 1) lse_nat[lg * rows_pad + row] = M + logf(Z);
+        else stats[(lg * n_split + split) * rows_pad + row] = make_float2(M, Z);
     }
+}
+
+__global__ void score_merge_f32(const float2* __restrict__ stats, int n_groups, int n_split,
+                                int rows_pad, int n_rows, float* __restrict__ lse_nat) {
+    const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
+    if (i >= (long)n_groups * rows_pad || i % rows_pad >= n_rows) return;
+    const float2* s = stats + i / rows_pad * n_split * rows_pad + i % rows_pad;
+    float M = -INFINITY, Z = 0.f;
+#pragma unroll 8                                         // (loads in flight, in-order sum)
+    for (int j = 0; j < n_split; ++j) M = fmaxf(M, s[(size_t)j * rows_pad].x);
+#pragma unroll 8
+    for (int j = 0; j < n_split; ++j) Z += s[(size_t)j * rows_pad].y * expf(s[(size_t)j * rows_pad].x - M);
+    lse_nat[i] = M + logf(Z);
 }
 
 // Column sums: a workgroup takes 32 keys of a layer; its waves share out the (KV
@@ -766,6 +786,20 @@ hipError_t launch_score_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, 
     return hipGetLastError();
 }
 
+// Keys per workgroup of the float32 statistics: a workgroup's rounds of 512 keys are a
+// serial chain, so few row blocks over many keys are split until there is a workgroup
+// for every CU (one workgroup per row before the MFMA kernels: 286 us for one layer of
+// 30000 keys with 64 rows, 186 for 8000 with 24).  Self-contained scores in us, one
+// split / two / the rule: 2 layers of 1024 keys (4 row blocks in all) 27.0 / 22.9 / 22.9,
+// of 2000 keys 37.6 / 26.6 / 20.3, one of 8000 (8) 188 / 111 / 37, of 30000 (2) 418 / 227
+// / 38, 2 of 2000 (128) 106 / 88 / 87, 4 of 3000 (256) 182 / 189 / 182.
+int f32_stats_split(const relaxkv_problem& p) {
+    constexpr long kCUs = 256, kRound = kF32StatsWaves * 32;
+    const long wg = (long)(round_up32(p.n_query * (p.H / p.H_kv)) / 32) * p.H_kv * p.L;
+    const long rounds = (p.T_c + kRound - 1) / kRound, per = (rounds * wg + kCUs - 1) / kCUs;
+    return (int)((per < rounds ? per : rounds) * kRound);
+}
+
 template <int D>
 hipError_t launch_score_f32(const relaxkv_problem& p, const ScoreWorkspace& w, char* ws,
                             float* scores, hipStream_t st, float scale) {
@@ -774,10 +808,18 @@ hipError_t launch_score_f32(const relaxkv_problem& p, const ScoreWorkspace& w, c
     const float* kc = (const float*)p.k_cache;
     float* part = (float*)(ws + w.part_off);
     float* lse = (float*)(ws + w.lse_off);
-    if (!p.q_lse)
-        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32, p.H_kv, p.L),
+    if (!p.q_lse) {
+        float2* stats = (float2*)(ws + w.stats_off);
+        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32 * w.n_split, p.H_kv, p.L),
                            dim3(kF32StatsWaves * 64), 0, st, q, kc, kv_strides(p), p.T_c, p.n_query,
-                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, scale, lse);
+                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, f32_stats_split(p), w.n_split,
+                           scale, stats, lse);
+        const long n = (long)p.L * p.H_kv * w.rows_pad;
+        if (w.n_split > 1)
+            hipLaunchKernelGGL(score_merge_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
+                               (const float2*)stats, p.L * p.H_kv, w.n_split, w.rows_pad, p.n_query * G,
+                               lse);
+    }
     hipLaunchKernelGGL(score_colsum_f32<D>, dim3((p.T_c + 31) / 32, p.L), dim3(kF32Waves * 64), 0, st,
                        q, kc, kv_strides(p), p.T_c, p.n_query, p.H, p.H_kv, G, p.n_query * G,
                        w.rows_pad, scale, lse, p.q_lse, part);
@@ -793,13 +835,13 @@ ScoreWorkspace score_workspace_layout(const relaxkv_problem& p) {
     const int G = p.H / p.H_kv;
     const bool bf = p.dtype == RELAXKV_DTYPE_BF16;
     w.rows_pad = round_up32(p.n_query * G);
-    const int kps = stats_split(p);
+    const int kps = bf ? stats_split(p) : f32_stats_split(p);
     w.n_split = (p.T_c + kps - 1) / kps;
     w.n_part = bf ? p.H_kv : 1;
     w.part_off = 0;
     size_t off = al((size_t)p.L * w.n_part * p.T_c * sizeof(float));
     w.stats_off = off;
-    if (bf) off += al((size_t)p.L * p.H_kv * w.n_split * w.rows_pad * sizeof(float2));
+    if (bf || w.n_split > 1) off += al((size_t)p.L * p.H_kv * w.n_split * w.rows_pad * sizeof(float2));
     w.lse_off = off;
     off += al((size_t)p.L * p.H_kv * w.rows_pad * sizeof(float));
     w.n_blk = (p.T_c + kFinKeys - 1) / kFinKeys;

@@ -62,3 +62,14 @@ def test_f32_rows(gpu_lib, T, H, H_kv, Qn, n, d):
                                                                    k_q, v_q)))
     assert_close(out.cpu().numpy(), O_ref, w, "query out")
     assert_close(lse.cpu().numpy(), lse_ref, w, "query lse")
+
+
+# few row blocks over many keys: the scores' row statistics take key splits (4, 3 and 3
+# of them; the last of one key, a partial round, a partial round after several)
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("L,T,H,H_kv,Qn", [(1, 1537, 2, 2, 1), (2, 1500, 6, 2, 30), (2, 9000, 8, 4, 130)])
+def test_f32_score_splits(gpu_lib, L, T, H, H_kv, Qn, d):
+    w = synth.shrink(W, L=L, T_c=T, H=H, H_kv=H_kv, Qn=Qn, d=d)
+    case = Case(w)
+    a_ref, _, _ = case.oracle_scores()
+    assert_close(case.gpu_scores().cpu().numpy(), a_ref, w, "scores")
