@@ -61,6 +61,73 @@ __device__ __forceinline__ int lower_bound16(const int32_t* __restrict__ a, int 
     return lo;
 }
 
+// Past this many layers sets_blocks finds and marks the anchors of several layers at a
+// time (MANY: their searches and loads together), and sums the positions by h (LDS
+// atomics) and then over the layers, instead of once per layer.  One workgroup per
+// block goes through all layers, so with many of them and few blocks these chains
+// were longer than the four launches before (16.5 us at 128 layers of 64 positions, 54
+// at 1024 of 1024).  Both launches in us, without / with it: 8 layers of 1531 positions
+// 9.4 / 11.1, 40 of 32768 18.1 / 18.6, 64 of 1024 12.8 / 14.8, 128 of 1024 19.4 / 16.2,
+// 512 of 4096 78 / 50, 1024 of 64 69 / 23, 1024 of 1024 106 / 48.
+constexpr int kFewLayers = 64;
+static_assert(RELAXKV_MAX_LAYERS <= kSetThreads, "one layer per thread");
+
+// lower_bound16 of N lists at once.
+template <int N>
+__device__ __forceinline__ void lower_bounds16(const int32_t* const (&a)[N], int n, const int (&v)[N],
+                                               int (&lo)[N]) {
+    const int j = threadIdx.x & 15, shift = threadIdx.x & 48;
+    int hi[N];
+    bool any_open = n > 0;
+#pragma unroll
+    for (int x = 0; x < N; ++x) {
+        lo[x] = 0;
+        hi[x] = n;
+    }
+    while (__any(any_open)) {
+        int e[N];
+#pragma unroll
+        for (int x = 0; x < N; ++x)
+            e[x] = lo[x] < hi[x] ? a[x][lo[x] + (j + 1) * (hi[x] - lo[x]) / 17] : 0;
+        any_open = false;
+#pragma unroll
+        for (int x = 0; x < N; ++x) {
+            const bool open = lo[x] < hi[x];
+            const int m = hi[x] - lo[x], base = lo[x];
+            const int c = __popc((uint32_t)(__ballot(open && e[x] < v[x]) >> shift) & 0xffffu);
+            if (open) {
+                if (c > 0) lo[x] = base + c * m / 17 + 1;
+                if (c < 16) hi[x] = base + (c + 1) * m / 17;
+            }
+            any_open |= lo[x] < hi[x];
+        }
+    }
+}
+
+// The parts of the ascending anchor rows that lie in [v0, v1), four layers per group
+// of 16 lanes at a time.
+__device__ __forceinline__ void block_segments(const int32_t* __restrict__ anchors, int L, int k,
+                                               int v0, int v1, int* seg_lo, int* seg_hi) {
+    constexpr int NG = kSetThreads / 16, NL = 4;
+    for (int l0 = threadIdx.x / 16; l0 < (L + NG - 1) / NG * NG; l0 += NL * NG) {
+        const int32_t* rows[2 * NL];
+        int v[2 * NL], at[2 * NL];
+#pragma unroll
+        for (int x = 0; x < NL; ++x) {
+            rows[2 * x] = rows[2 * x + 1] = anchors + (size_t)min(l0 + x * NG, L - 1) * k;
+            v[2 * x] = v0;
+            v[2 * x + 1] = v1;
+        }
+        lower_bounds16<2 * NL>(rows, k, v, at);
+#pragma unroll
+        for (int x = 0; x < NL; ++x)
+            if (l0 + x * NG < L && (threadIdx.x & 15) == 0) {
+                seg_lo[l0 + x * NG] = at[2 * x];
+                seg_hi[l0 + x * NG] = at[2 * x + 1];
+            }
+    }
+}
+
 // Per-block counts the first launch leaves for the second, in the scratch array of
 // the sets buffer, which no caller is given (a caller may pass one of the sets' lists
 // as the targets, or keep using them after the build).  Anchor targets: n, e, f
@@ -81,7 +148,7 @@ static_assert((long)kMaxSetBlock * (kMaxSetBlock + 1) / 2 <= INT32_MAX && kMaxSe
 // One workgroup per block of positions: h of the block and the counts above (GT:
 // of the targets P instead of R_l; h is written by the second launch).  Also
 // zeroes the attention's work counters.
-template <bool GT>
+template <bool GT, bool MANY>
 __global__ __launch_bounds__(kSetThreads) void sets_blocks(
     const int32_t* __restrict__ anchors, int L, int k, int T, int pb,
     const int32_t* __restrict__ P, const int32_t* __restrict__ n_P, int32_t* __restrict__ h,
@@ -95,13 +162,22 @@ __global__ __launch_bounds__(kSetThreads) void sets_blocks(
     const int b0 = b * pb, len = min(pb, T - b0);
     for (int i = b * kSetThreads + tid; i < n_tiles; i += n_blk * kSetThreads) tiles[i] = 0u;
     for (int i = tid; i < pb; i += kSetThreads) hl[i] = -1;
-    for (int l0 = 0; l0 < L; l0 += kSetThreads / 16) {
-        const int l = l0 + tid / 16;
-        const int32_t* row = anchors + (size_t)min(l, L - 1) * k;
-        const int lo = lower_bound16(row, k, b0), hi = lower_bound16(row, k, b0 + len);
-        if (l < L && (tid & 15) == 0) {
-            seg_lo[l] = lo;
-            seg_hi[l] = hi;
+    if (MANY && n_blk == 1) {
+        for (int l = tid; l < L; l += kSetThreads) {
+            seg_lo[l] = 0;
+            seg_hi[l] = k;
+        }
+    } else if (MANY) {
+        block_segments(anchors, L, k, b0, b0 + len, seg_lo, seg_hi);
+    } else {
+        for (int l0 = 0; l0 < L; l0 += kSetThreads / 16) {
+            const int l = l0 + tid / 16;
+            const int32_t* row = anchors + (size_t)min(l, L - 1) * k;
+            const int lo = lower_bound16(row, k, b0), hi = lower_bound16(row, k, b0 + len);
+            if (l < L && (tid & 15) == 0) {
+                seg_lo[l] = lo;
+                seg_hi[l] = hi;
+            }
         }
     }
     if (GT && w == 0) {                                  // lanes 0-15: b0, the others: b0 + len
@@ -111,16 +187,76 @@ __global__ __launch_bounds__(kSetThreads) void sets_blocks(
         if (lane < 3) sums[lane] = 0;
     }
     __syncthreads();
-    for (int l = w; l < L; l += kSetThreads / 64) {
-        const int32_t* row = anchors + (size_t)l * k;
-        for (int j = seg_lo[l] + lane; j < seg_hi[l]; j += 64) {
-            const int i = row[j] - b0;
-            if (i >= 0 && i < len) atomicMax(&hl[i], l);
+    if constexpr (MANY) {
+        constexpr int NX = 4, NWV = kSetThreads / 64;    // NX layers of a wave in flight
+        for (int l0 = w; l0 < L; l0 += NX * NWV) {
+            int at[NX];
+#pragma unroll
+            for (int x = 0; x < NX; ++x) {               // (past the last layer it is marked again)
+                const int l = min(l0 + x * NWV, L - 1), j = seg_lo[l] + lane;
+                at[x] = j < seg_hi[l] ? anchors[(size_t)l * k + j] - b0 : -1;
+            }
+#pragma unroll
+            for (int x = 0; x < NX; ++x) {
+                const int l = min(l0 + x * NWV, L - 1);
+                if (at[x] >= 0 && at[x] < len) atomicMax(&hl[at[x]], l);
+                for (int j = seg_lo[l] + 64 + lane; j < seg_hi[l]; j += 64) {
+                    const int i = anchors[(size_t)l * k + j] - b0;
+                    if (i >= 0 && i < len) atomicMax(&hl[i], l);
+                }
+            }
+        }
+    } else {
+        for (int l = w; l < L; l += kSetThreads / 64) {
+            const int32_t* row = anchors + (size_t)l * k;
+            for (int j = seg_lo[l] + lane; j < seg_hi[l]; j += 64) {
+                const int i = row[j] - b0;
+                if (i >= 0 && i < len) atomicMax(&hl[i], l);
+            }
         }
     }
     __syncthreads();
     if constexpr (!GT) {
         for (int i = tid; i < len; i += kSetThreads) h[b0 + i] = hl[i];
+        if constexpr (MANY) {
+            __shared__ int by_f[RELAXKV_MAX_LAYERS];     // (the other sums in the segments' arrays)
+            int *by_n = seg_lo, *by_e = seg_hi;
+            for (int l = tid; l < L; l += kSetThreads) by_n[l] = by_e[l] = by_f[l] = 0;
+            const int per = max(64, pb / (kSetThreads / 64)), s0 = w * per;   // positions of a wave
+            int u = 0;
+            if (s0 < pb)
+                for (int c = s0; c < s0 + per; c += 64) u += __popcll(__ballot(hl[c + lane] >= 0));
+            if (lane == 0) wave_n[w] = u;
+            __syncthreads();
+            u = 0;
+            for (int ww = 0; ww < w; ++ww) u += wave_n[ww];
+            if (s0 < pb)
+                for (int c = s0; c < s0 + per; c += 64) {
+                    const int hv = hl[c + lane];
+                    const uint64_t mu = __ballot(hv >= 0);
+                    if (hv >= 0) {
+                        atomicAdd(&by_n[hv], 1);
+                        if (n_blk > 1) {
+                            atomicAdd(&by_e[hv], u + lanes_below(mu) + 1);
+                            atomicAdd(&by_f[hv], c + lane + 1);
+                        }
+                    }
+                    u += __popcll(mu);
+                }
+            __syncthreads();
+            const int l = L - 1 - tid;
+            int32_t* const to[3] = {sc.n, sc.e, sc.f};
+            const int* const by[3] = {by_n, by_e, by_f};
+#pragma unroll
+            for (int x = 0; x < 3; ++x) {
+                if (x > 0 && n_blk == 1) break;
+                int tot;
+                const int v = l >= 0 ? by[x][l] : 0;
+                const int sum = block_exclusive_scan<kSetThreads>(v, wave_n, tot) + v;
+                if (l >= 0) to[x][(size_t)l * n_blk + b] = sum;
+            }
+            return;
+        }
         for (int l = w; l < L; l += kSetThreads / 64) {
             int n = 0, u = 0, e = 0, f = 0;
             for (int c = 0; c < pb; c += 64) {
@@ -536,9 +672,13 @@ BlockScratch block_scratch(const relaxkv_problem& p, const relaxkv_sets& s, int 
 template <bool GT>
 void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, const BlockScratch& sc,
                    const int32_t* P, const int32_t* n_P, hipStream_t st) {
-    hipLaunchKernelGGL(sets_blocks<GT>, dim3(set_blocks(p, pb)), dim3(kSetThreads),
-                       pb * sizeof(int), st, s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, sc, s.tiles,
-                       (int)attn_tile_words(p));
+    auto go = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(set_blocks(p, pb)), dim3(kSetThreads), pb * sizeof(int), st,
+                           s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, sc, s.tiles,
+                           (int)attn_tile_words(p));
+    };
+    if (p.L > kFewLayers) go(sets_blocks<GT, true>);
+    else go(sets_blocks<GT, false>);
 }
 
 // The anchors' union and targets; without LISTS only U, cidx, R_off and the counts.

@@ -55,6 +55,13 @@ def test_set_blocks(gpu_lib, L, T):
         compare_global_sets(gpu_global_sets(case, P), oracle.build_sets_global(anchors, T, P))
 
 
+# around the layer counts where the blocks are counted by h and several layers are
+# searched at a time
+@pytest.mark.parametrize("L,T", [(64, 300), (65, 256), (65, 16385), (200, 2000), (321, 5000)])
+def test_set_blocks_many_layers(gpu_lib, L, T):
+    test_set_blocks(gpu_lib, L, T)
+
+
 @pytest.mark.parametrize("T", [31, 33, 1025, 1 << 18, (1 << 18) + 1])
 @pytest.mark.parametrize("construction", ["global", "layerwise"])
 def test_context_limits(gpu_lib, T, construction):
