@@ -434,6 +434,9 @@ __global__ void score_merge(const float2* __restrict__ stats, int n_groups, int 
 // heads, d 128, 8.06 -> 0.53 ms; 2 layers of 1024 keys, 4q/2kv heads 44 -> 23 us.
 constexpr int kF32Waves = 8;            // of the column sums
 constexpr int kF32StatsWaves = 16;
+constexpr int kF32Unit = kF32StatsWaves * 32;            // keys per unit of the row statistics
+constexpr int kF32Batch = 8;                             // units between two barriers
+constexpr int kF32Table = 64;                            // most units a workgroup merges itself
 
 template <int D>
 __device__ __forceinline__ void load_row_f32(f32x4 (&dst)[D / 8], const float* p, int hf) {
@@ -451,73 +454,100 @@ __device__ __forceinline__ f32x16 dot_f32(const f32x4 (&a)[D / 8], const f32x4 (
     return s;
 }
 
-// Natural-log normalisers: a workgroup takes 32 (token, head) rows of a KV head of a
-// layer and one of n_split splits of the keys (see f32_stats_split); its waves take the
-// 32-key blocks in turn (S^T = K Q^T, one row per lane), each with its own running
-// (max, sum), merged in wave order.  Of several splits it leaves its (max, sum), which
-// score_merge_f32 merges in split order.
+// Row statistics over units of 512 keys: a workgroup takes 32 (token, head) rows of a KV
+// head of a layer and `per` consecutive units, one 32-key block per wave and unit (S^T
+// = K Q^T, one row per lane; Q staged in LDS, the next unit's K loaded behind this
+// one's products).  Every kF32Batch units the waves' (max, sum) of each unit are merged
+// in wave order, a wave per unit; the units' pairs are merged in order, by the workgroup
+// if it has them all (and they fit its table), else by score_merge_f32: the same bits
+// however the units are spread over workgroups.
+__device__ __forceinline__ float merge_units_f32(const float2* __restrict__ s, int n, size_t stride) {
+    float M = -INFINITY, Z = 0.f;
+#pragma unroll 8                                         // (loads in flight, in-order sum)
+    for (int j = 0; j < n; ++j) M = fmaxf(M, s[j * stride].x);
+#pragma unroll 8
+    for (int j = 0; j < n; ++j) Z += s[j * stride].y * expf(s[j * stride].x - M);
+    return M + logf(Z);
+}
+
 template <int D>
 __global__ __launch_bounds__(kF32StatsWaves * 64) void score_stats_f32(
     const float* __restrict__ q, const float* __restrict__ kc, KvStrides ks, int T, int Qn, int H,
-    int Hkv, int G, int n_rows, int rows_pad, int keys_per_split, int n_split, float scale,
+    int Hkv, int G, int n_rows, int rows_pad, int n_unit, int per, float scale,
     float2* __restrict__ stats, float* __restrict__ lse_nat) {
-    __shared__ float red_m[kF32StatsWaves][32], red_z[kF32StatsWaves][32];
+    __shared__ f32x4 Qs[D / 8][64];
+    __shared__ float2 red[kF32Batch][kF32StatsWaves][32], table[kF32Table][32];
     const int g = blockIdx.y, l = blockIdx.z;
-    const int rb = blockIdx.x / n_split, split = blockIdx.x - rb * n_split;
-    const int key1 = min(T, (split + 1) * keys_per_split);
+    const int n_split = (n_unit + per - 1) / per;
+    const int rb = blockIdx.x / n_split, u0 = (blockIdx.x - rb * n_split) * per;
+    const int u1 = min(n_unit, u0 + per);
+    const bool own = n_split == 1 && n_unit <= kF32Table;
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hf = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = rb * 32 + r32, rr = min(row, n_rows - 1);
+    const size_t lg = (size_t)l * Hkv + g;
     const float* Kg = kc + l * ks.layer + g * ks.head;
-    f32x4 qf[D / 8], kf[D / 8];
-    load_row_f32<D>(qf, q + (((size_t)l * Qn + rr / G) * H + g * G + rr % G) * D, hf);
-    float m = -INFINITY, z = 0.f;
-    for (int k0 = split * keys_per_split + w * 32; k0 < key1; k0 += kF32StatsWaves * 32) {
-        load_row_f32<D>(kf, Kg + min(k0 + r32, T - 1) * ks.token, hf);
-        f32x16 s = dot_f32<D>(kf, qf);
-        const int ex = key1 - 1 - k0 - 4 * hf;           // last key of the block
-        float mx = m;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) {
-            s[v] = 8 * (v >> 2) + (v & 3) > ex ? -INFINITY : s[v] * scale;
-            mx = fmaxf(mx, s[v]);
-        }
-        const float ref = mx == -INFINITY ? 0.f : mx;    // (a half-wave past the last key)
-        z *= expf(m - ref);
-        m = mx;
-#pragma unroll
-        for (int v = 0; v < 16; ++v) z += expf(s[v] - ref);
-    }
-    // the two half-waves of a row, then the waves
-    const float m2 = __shfl_xor(m, 32, 64), z2 = __shfl_xor(z, 32, 64);
-    const float mw = fmaxf(m, m2);
-    if (hf == 0) {
-        red_m[w][r32] = mw;
-        red_z[w][r32] = mw == -INFINITY ? 0.f : z * expf(m - mw) + z2 * expf(m2 - mw);
-    }
+    f32x4 kf[D / 8];
+    auto load_k = [&](int u) {
+        load_row_f32<D>(kf, Kg + min(u * kF32Unit + w * 32 + r32, T - 1) * ks.token, hf);
+    };
+    load_k(u0);
+    const float* qrow = q + (((size_t)l * Qn + rr / G) * H + g * G + rr % G) * D;
+    for (int j = w; j < D / 8; j += kF32StatsWaves) Qs[j][lane] = *(const f32x4*)(qrow + 8 * j + 4 * hf);
     __syncthreads();
-    if (tid < 32 && row < n_rows) {
-        float M = -INFINITY, Z = 0.f;
-        for (int i = 0; i < kF32StatsWaves; ++i) M = fmaxf(M, red_m[i][r32]);
-        for (int i = 0; i < kF32StatsWaves; ++i)
-            if (red_m[i][r32] != -INFINITY) Z += red_z[i][r32] * expf(red_m[i][r32] - M);
-        const size_t lg = (size_t)l * Hkv + g;
-        if (n_split == 1) lse_nat[lg * rows_pad + row] = M + logf(Z);
-        else stats[(lg * n_split + split) * rows_pad + row] = make_float2(M, Z);
+    for (int u = u0; u < u1; ++u) {
+        float m = -INFINITY, z = 0.f;
+        const int k0 = u * kF32Unit + w * 32;
+        if (k0 < T) {
+            f32x16 s = f32x16{};
+#pragma unroll
+            for (int j = 0; j < D / 8; ++j) {
+                const f32x4 qj = Qs[j][lane];
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qj[i], s, 0, 0, 0);
+            }
+            if (u + 1 < u1) load_k(u + 1);
+            const int ex = T - 1 - k0 - 4 * hf;          // last key of the block
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                s[v] = 8 * (v >> 2) + (v & 3) > ex ? -INFINITY : s[v] * scale;
+                m = fmaxf(m, s[v]);
+            }
+            m = fmaxf(m, __shfl_xor(m, 32, 64));         // (the row's other half-wave)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) z += expf(s[v] - m);
+            z += __shfl_xor(z, 32, 64);
+        }
+        const int x = (u - u0) % kF32Batch;
+        if (hf == 0) red[x][w][r32] = make_float2(m, z);
+        if (x + 1 < kF32Batch && u + 1 < u1) continue;
+        __syncthreads();
+        if (w <= x && hf == 0) {
+            float M = -INFINITY, Z = 0.f;
+            for (int i = 0; i < kF32StatsWaves; ++i) M = fmaxf(M, red[w][i][r32].x);
+            for (int i = 0; i < kF32StatsWaves; ++i)     // (a wave past the last key adds 0 * exp(-inf))
+                Z += red[w][i][r32].y * expf(red[w][i][r32].x - M);
+            const int uw = u - x + w;
+            if (n_unit == 1) {
+                if (row < n_rows) lse_nat[lg * rows_pad + row] = M + logf(Z);
+            } else if (own) {
+                table[uw][r32] = make_float2(M, Z);
+            } else if (row < n_rows) {
+                stats[(lg * n_unit + uw) * rows_pad + row] = make_float2(M, Z);
+            }
+        }
+        __syncthreads();
     }
+    if (own && n_unit > 1 && tid < 32 && row < n_rows)   // (one unit: see above)
+        lse_nat[lg * rows_pad + row] = merge_units_f32(&table[0][r32], n_unit, 32);
 }
 
-__global__ void score_merge_f32(const float2* __restrict__ stats, int n_groups, int n_split,
+__global__ void score_merge_f32(const float2* __restrict__ stats, int n_groups, int n_unit,
                                 int rows_pad, int n_rows, float* __restrict__ lse_nat) {
     const long i = blockIdx.x * (long)blockDim.x + threadIdx.x;
     if (i >= (long)n_groups * rows_pad || i % rows_pad >= n_rows) return;
-    const float2* s = stats + i / rows_pad * n_split * rows_pad + i % rows_pad;
-    float M = -INFINITY, Z = 0.f;
-#pragma unroll 8                                         // (loads in flight, in-order sum)
-    for (int j = 0; j < n_split; ++j) M = fmaxf(M, s[(size_t)j * rows_pad].x);
-#pragma unroll 8
-    for (int j = 0; j < n_split; ++j) Z += s[(size_t)j * rows_pad].y * expf(s[(size_t)j * rows_pad].x - M);
-    lse_nat[i] = M + logf(Z);
+    lse_nat[i] = merge_units_f32(stats + i / rows_pad * n_unit * rows_pad + i % rows_pad, n_unit, rows_pad);
 }
 
 // Column sums: a workgroup takes 32 keys of a layer; its waves share out the (KV
@@ -786,18 +816,17 @@ hipError_t launch_score_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, 
     return hipGetLastError();
 }
 
-// Keys per workgroup of the float32 statistics: a workgroup's rounds of 512 keys are a
-// serial chain, so few row blocks over many keys are split until there is a workgroup
-// for every CU (one workgroup per row before the MFMA kernels: 286 us for one layer of
-// 30000 keys with 64 rows, 186 for 8000 with 24).  Self-contained scores in us, one
-// split / two / the rule: 2 layers of 1024 keys (4 row blocks in all) 27.0 / 22.9 / 22.9,
-// of 2000 keys 37.6 / 26.6 / 20.3, one of 8000 (8) 188 / 111 / 37, of 30000 (2) 418 / 227
-// / 38, 2 of 2000 (128) 106 / 88 / 87, 4 of 3000 (256) 182 / 189 / 182.
-int f32_stats_split(const relaxkv_problem& p) {
-    constexpr long kCUs = 256, kRound = kF32StatsWaves * 32;
+// Units per workgroup of the float32 statistics: as many splits as give each CU at most
+// one workgroup, since a workgroup's units are a serial chain.  Self-contained scores
+// in us, one workgroup per row and VALU / one per 32 rows and all keys / split: one
+// layer of 30000 keys and 64 rows 286 / 422 / 34, of 8000 and 24 rows 185 / 189 / 40, 2
+// of 2000 and 2 rows 29 / 37 / 21, 2 of 1024 and 32 rows 43 / 27 / 20, 4 of 3000 and
+// 2048 rows (256 workgroups: not split) 4997 / 186 / 184.
+int f32_stats_units(const relaxkv_problem& p) {
+    constexpr long kCUs = 256;
     const long wg = (long)(round_up32(p.n_query * (p.H / p.H_kv)) / 32) * p.H_kv * p.L;
-    const long rounds = (p.T_c + kRound - 1) / kRound, per = (rounds * wg + kCUs - 1) / kCUs;
-    return (int)((per < rounds ? per : rounds) * kRound);
+    const long n = (p.T_c + kF32Unit - 1) / kF32Unit, split = wg >= kCUs ? 1 : kCUs / wg;
+    return (int)((n + split - 1) / split);
 }
 
 template <int D>
@@ -810,12 +839,12 @@ hipError_t launch_score_f32(const relaxkv_problem& p, const ScoreWorkspace& w, c
     float* lse = (float*)(ws + w.lse_off);
     if (!p.q_lse) {
         float2* stats = (float2*)(ws + w.stats_off);
-        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32 * w.n_split, p.H_kv, p.L),
+        const int per = f32_stats_units(p), n_split = (w.n_split + per - 1) / per;
+        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32 * n_split, p.H_kv, p.L),
                            dim3(kF32StatsWaves * 64), 0, st, q, kc, kv_strides(p), p.T_c, p.n_query,
-                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, f32_stats_split(p), w.n_split,
-                           scale, stats, lse);
+                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, w.n_split, per, scale, stats, lse);
         const long n = (long)p.L * p.H_kv * w.rows_pad;
-        if (w.n_split > 1)
+        if (n_split > 1 || w.n_split > kF32Table)
             hipLaunchKernelGGL(score_merge_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
                                (const float2*)stats, p.L * p.H_kv, w.n_split, w.rows_pad, p.n_query * G,
                                lse);
@@ -835,7 +864,7 @@ ScoreWorkspace score_workspace_layout(const relaxkv_problem& p) {
     const int G = p.H / p.H_kv;
     const bool bf = p.dtype == RELAXKV_DTYPE_BF16;
     w.rows_pad = round_up32(p.n_query * G);
-    const int kps = bf ? stats_split(p) : f32_stats_split(p);
+    const int kps = bf ? stats_split(p) : kF32Unit;
     w.n_split = (p.T_c + kps - 1) / kps;
     w.n_part = bf ? p.H_kv : 1;
     w.part_off = 0;

@@ -64,12 +64,43 @@ def test_f32_rows(gpu_lib, T, H, H_kv, Qn, n, d):
     assert_close(lse.cpu().numpy(), lse_ref, w, "query lse")
 
 
-# few row blocks over many keys: the scores' row statistics take key splits (4, 3 and 3
-# of them; the last of one key, a partial round, a partial round after several)
+# The row statistics' 512-key units: 4 (the last of one key), 3 and 18 of them, each in
+# a workgroup of its own or several in one (past 8, several batches), merged by a launch.
 @pytest.mark.parametrize("d", [64, 128])
 @pytest.mark.parametrize("L,T,H,H_kv,Qn", [(1, 1537, 2, 2, 1), (2, 1500, 6, 2, 30), (2, 9000, 8, 4, 130)])
-def test_f32_score_splits(gpu_lib, L, T, H, H_kv, Qn, d):
+def test_f32_score_units(gpu_lib, L, T, H, H_kv, Qn, d):
     w = synth.shrink(W, L=L, T_c=T, H=H, H_kv=H_kv, Qn=Qn, d=d)
     case = Case(w)
     a_ref, _, _ = case.oracle_scores()
     assert_close(case.gpu_scores().cpu().numpy(), a_ref, w, "scores")
+
+
+@pytest.mark.parametrize("T", [512, 1025, 4600, 9300])
+def test_f32_layer_scores_do_not_depend_on_the_other_layers(gpu_lib, T):
+    """One layer (a unit per workgroup) and 64 (8 workgroups of each layer, 512 in all,
+    that take every unit): the same bits."""
+    w = synth.shrink(W, L=64, T_c=T, H=8, H_kv=8, Qn=5, d=64)
+    q, kc, vc = synth.make_cache(w, "cuda")
+
+    def scores(n):
+        req = relaxkv.Request(q[:n], kc[:n], vc[:n], w.ratio)
+        a = torch.empty(n, T, device="cuda")
+        req.score(req.alloc_workspace(), a)
+        return a
+    assert torch.equal(scores(64)[:1], scores(1)) and torch.equal(scores(64)[:7], scores(7))
+
+
+def test_f32_score_more_units_than_a_workgroup_merges(gpu_lib):
+    """65 units, all in the one workgroup of each of 256 KV heads."""
+    T, H, d = 64 * 512 + 3, 256, 64
+    g = torch.Generator(device="cuda").manual_seed(5)
+    q = torch.randn(1, 1, H, d, device="cuda", generator=g)
+    k = torch.randn(1, H, T, d, device="cuda", generator=g)
+    req = relaxkv.Request(q, k, k, 0.1)
+    a = torch.empty(1, T, device="cuda")
+    req.score(req.alloc_workspace(), a)
+    p = torch.zeros(T, dtype=torch.float64, device="cuda")
+    for h in range(H):
+        p += torch.softmax(k[0, h].double() @ q[0, 0, h].double() / d ** 0.5, 0)
+    ref = ((p - p.min()) / (p.max() - p.min())).cpu().numpy()
+    assert_close(a[0].cpu().numpy(), ref, synth.shrink(W, T_c=T), "scores")
