@@ -173,7 +173,8 @@ typedef struct relaxkv_problem {
  *                          builds (relaxkv_build_sets, relaxkv_build_sets_global)
  *                          leave it and g as they are.
  *   g        [T_c]         float32 layer-mean scores of the last Global Sparse build.
- *   tiles    [2][L][H_kv+1] uint32 work counters of the bf16 attention, one slot per
+ *   tiles    [2][L][H_kv+1] uint32 work counters of the bf16 attention's larger launches
+ *                          (smaller ones map workgroups to tiles directly), one slot per
  *                          context mode (0: the layer's context list, 1: Full-Prefix
  *                          Control) and layer: a next-tile counter per KV head and a
  *                          count of the launch's workgroups.  Zeroed by every set build;
@@ -253,6 +254,10 @@ relaxkv_status relaxkv_sets_bind(const relaxkv_problem* p, void* dev_buf, size_t
  *   ws       device scratch of ws_bytes >= relaxkv_score_workspace_bytes(p).
  *   scores   device out [L][T_c] float32, a_{l,i} in [0, 1].
  * Reads q, k_cache and (optionally) q_lse of `p`; never reads v_cache.
+ * The same call gives the same bits on every run.  A layer's scores are also the
+ * same bits whatever other layers the problem holds, except for self-contained bf16
+ * scores of at most 4096 positions: the key splits of their row statistics, and with
+ * them the last bits, are chosen by the size of the whole problem.
  */
 relaxkv_status relaxkv_score(const relaxkv_problem* p, void* ws, size_t ws_bytes,
                              float* scores, void* stream);
@@ -369,8 +374,11 @@ relaxkv_status relaxkv_build_sets_global(const relaxkv_problem* p, relaxkv_sets*
  * naive cache of the layer is read from p->k_cache / p->v_cache.  A target
  * whose context is empty (only with the lists of relaxkv_build_sets_global or
  * relaxkv_build_sets_context, union context) gets O = 0 and lse = -inf.
- * The bf16 kernel's workgroups take their tiles from the s->tiles slot of this
- * layer and context mode (dynamic balancing across XCDs whose clocks differ):
+ * The same call gives the same bits on every run.  n_rows (up to the bound of the
+ * lists) also chooses the kernel: few rows are split over more workgroups, which sum a
+ * row's keys in another order, so the last bits may differ between two values of n_rows.
+ * The workgroups of the larger bf16 launches take their tiles from the s->tiles slot
+ * of this layer and context mode (dynamic balancing across XCDs whose clocks differ):
  * two launches with the same sets, layer and context mode must not overlap in
  * time (stream-ordered calls are fine); launches for other layers or modes may.
  */

@@ -510,11 +510,12 @@ def test_attention_concurrent_layers_and_modes(gpu_lib):
 
 
 def test_colsum_split_does_not_change_scores(gpu_lib):
-    """The column-sum pass takes 4096- or 8192-key splits, whichever needs fewer
+    """The column-sum pass takes 512- to 8192-key splits, whichever needs the fewest
     key-steps per CU for the problem's size; a key's column sum does not depend
-    on the split.  Layer 0 of an 8K context is scored inside a 64-layer problem
-    (8192-key splits) and alone (4096-key splits): the same bits in both scoring
-    modes, and within the bf16 tolerance of the oracle."""
+    on the split, and past 4096 keys the row statistics' split is fixed.  Layer 0 of an
+    8K context is scored inside a 64-layer problem (8192-key splits) and alone
+    (512-key splits): the same bits in both scoring modes, and within the bf16
+    tolerance of the oracle."""
     w = synth.shrink(synth.WORKLOADS["llama8b-8k"], L=64)
     q, kc, vc = synth.make_cache(w, "cuda")
     g = torch.Generator(device="cuda").manual_seed(7)
