@@ -35,8 +35,7 @@ SMALL = {
     "long-query": synth.shrink(W["qwen14b-16k"], L=2, T_c=1300, Qn=100),
     "gqa16": synth.shrink(W["llama8b-8k"], L=2, T_c=900, H=32, H_kv=2, Qn=8),
     "gqa12-d64": synth.shrink(W["llama8b-8k"], L=3, T_c=1100, H=24, H_kv=2, d=64, Qn=12),
-    # more KV heads than XCDs, and a KV-head count that does not divide their number:
-    # the attention's per-head tile counters start workgroups on every head
+    # more KV heads than XCDs, and a KV-head count that does not divide their number
     "kv16": synth.shrink(W["llama8b-8k"], L=2, T_c=1000, H=32, H_kv=16, Qn=8),
     "kv3": synth.shrink(W["llama8b-8k"], L=2, T_c=1000, H=12, H_kv=3, Qn=8),
     # G = 7 and G = 10 do not divide the 384 rows of an attention tile: tiles begin and
@@ -429,12 +428,12 @@ def test_row_capacity_clamps_and_reports(gpu_lib, name):
 
 
 def test_attention_tile_counters(gpu_lib):
-    """The bf16 attention's workgroups take their tiles from per-layer, per-mode
-    counters in the sets buffer: a set build zeroes every slot whatever the
-    buffer held, each launch returns its slot to zero, every target is computed
-    exactly once (outputs against the oracle on every target), and repeated
-    launches, interleaved across layers and modes on one stream, give the same
-    bits."""
+    """The bf16 attention's larger launches take their tiles from per-layer, per-mode
+    counters in the sets buffer (test_gpu_attn_counters.py); launches of this size map
+    workgroups to tiles directly.  A set build zeroes every slot whatever the buffer
+    held, these launches leave them zero, every target is computed exactly once (outputs
+    against the oracle on every target), and repeated launches, interleaved across
+    layers and modes on one stream, give the same bits."""
     w = SMALL["qwen-planted"]
     case = Case(w)
     a = synthetic_scores(case.L, case.T, seed=23)
@@ -469,10 +468,10 @@ def test_attention_tile_counters(gpu_lib):
 
 def test_attention_concurrent_layers_and_modes(gpu_lib):
     """Launches for different layers, and for the two context modes of one
-    layer, may run at the same time (each takes its tiles from its own counter
-    slot): three launches on three streams with no ordering between them give
-    the bits of the same launches run one after another, and every slot is back
-    at zero afterwards."""
+    layer, may run at the same time (test_gpu_attn_counters.py has those that take
+    their tiles from counters): four launches on four streams with no ordering between
+    them give the bits of the same launches run one after another, and every slot is
+    zero afterwards."""
     w = SMALL["qwen-planted"]
     case = Case(w)
     a = synthetic_scores(case.L, case.T, seed=29)
