@@ -43,7 +43,12 @@ constexpr int kQaKeys = 64;            // keys per tile
 #define QA_NH 2
 #endif
 constexpr int kQaStages = RELAXKV_QA_STAGES;   // LDS ring depth (a K and a V tile per stage)
-constexpr int kQaMinSplit = 256;       // fewest cache keys per split
+// Fewest cache keys per split.  A call in us with 64 / 128 / 256 / 512 (24 query tokens, 32
+// heads of 8 KV heads, d 128): 600 keys 13.6 / 15.1 / 14.5 / 18.7, 1531 keys 14.2 / 15.3 /
+// 17.8 / 22.0 (4 tokens 11.9 / 13.3 / 16.4 / 20.5, 64 tokens 19.4 / 19.1 / 22.0 / 26.9), 6000
+// keys 14.9 / 14.9 / 16.1 / 20.3; 4000 keys, 14 heads of 2: 18.3 / 13.3 / 16.6 / 22.2.  So 512 is
+// too many everywhere, and 64 or 128 would gain 1-4 us on short contexts.
+constexpr int kQaMinSplit = 256;
 constexpr int kQaMaxSplit = 4096;      // most cache keys per split
 constexpr int kQaRing = 4;             // K fragments read ahead of their MFMA
 constexpr float kQaSlack = 8.0f;       // log2 units the running max may lag the true max
@@ -140,7 +145,7 @@ __global__ __launch_bounds__((NB + NH) * 64) void qattn_bf16(QaArgs a) {
     // ASM_FILL: after the builtin the compiler waits for every load in flight before
     // the step's V reads; the assembly form leaves the waiting to wait_tile (13
     // query tokens over 32K, 8 KV heads: 35.1 -> 32.2 us, 32 tokens 38.3 -> 33.8,
-    // 128 tokens 86 -> 81; the ten-block kernel is issue-bound and did not gain).
+    // 128 tokens 86 -> 81; the ten-block kernel did not gain: 64-66 against 64).
     auto fill = [&](const uint16_t* src, uint16_t* dst) {
         if constexpr (ASM_FILL) fill_lds16(src, lds_addr(dst));
         else load_lds16(src, dst);

@@ -12,12 +12,14 @@
 // fragment read from LDS feeds two MFMAs):
 //   1. score_stats_kreg -- S^T = K Q^T (one query row per lane): each row's
 //      (reference, sum of exp2) over the split.           [skipped with q_lse]
-//   2. score_merge  -- per row, merge the splits into a log2-sum-exp.
+//   2. score_merge  -- per row, merge the splits into a log2-sum-exp (few splits and rows:
+//      merged by pass 3's workgroups instead).
 //   3. score_colsum_kreg -- S = Q K^T - lse (one key per lane; each
 //      accumulator starts at its row's -lse), summing exp2 over the rows: the
 //      pooled mass of each key for this KV head.
 //   4. score_pool / score_minmax -- the fixed-order sum over KV heads and the
-//      1/(H Qn) factor with per-block extrema, then the MinMax normalisation.
+//      1/(H Qn) factor with per-block extrema, then the MinMax normalisation
+//      (score_finish for short contexts: both in one launch).
 // float32 path: float32 MFMA kernels with the same four steps (used for fp32
 // inputs, where bf16 MFMA would not meet fp32 accuracy).
 // Every reduction has a fixed order and no float atomics: results are
