@@ -106,34 +106,16 @@ __device__ __forceinline__ float merge_stats(const float2* __restrict__ s, int n
     return M + __log2f(Z);
 }
 
-// Up to this many splits and rows the column-sum workgroups merge the statistics of
-// their rows themselves while they stage them, which saves a launch; past either a
-// launch of its own merges each row once (every workgroup of a long row set would
-// merge all of it).  Self-contained scores in us, launch / inline: 8 layers of 1531
-// keys (24 query tokens, 8 KV heads) 25.9 / 23.4, 32 of 8192 326 / 321, one layer of
-// 32768 with 320 rows (8 splits) 108 / 104, 8 of them 384 / 385, 40 of them 1892 /
-// 1889; 2048 rows of 4096 keys (8 splits) 195 / 193; 4 layers of 3000 keys with 16000
-// rows 1094 / 1106.
-constexpr int kMergeInlineRows = 2048;
+// Up to this many splits, and for row sets of one chunk, the column-sum workgroups
+// merge the statistics of their rows themselves while they stage them, which saves a
+// launch; else a launch of its own merges each row once (every workgroup of a longer row
+// set would merge all of it, chunk by chunk).  Self-contained scores in us, launch /
+// inline: 8 layers of 1531 keys (24 query tokens, 8 KV heads) 25.7 / 23.6, 32 of 8192
+// 314 / 313, 40 of 16384 934 / 927, 8 of 32768 (320 rows, 8 splits) 378 / 371, 40 of them
+// 1829 / 1820; 1024 rows of 2048 keys 98.8 / 100.1, 2048 rows of 4096 keys 189 / 202,
+// 16000 rows of 3000 keys, 4 layers, 1092 / 1176.  (All splits' loads in flight at once
+// made the merge shorter and the main loop behind it 0.4 to 1.6% longer.)
 constexpr int kMergeInline = 8;
-
-// merge_stats for n_split <= kMergeInline, the same operations in the same order with
-// every load in flight at once (one after the other they cost a workgroup 9 us at
-// eight splits).
-__device__ __forceinline__ float merge_stats_inline(const float2* __restrict__ s, int n_split,
-                                                    int rows_pad) {
-    float2 v[kMergeInline];
-#pragma unroll
-    for (int j = 0; j < kMergeInline; ++j) v[j] = s[(size_t)min(j, n_split - 1) * rows_pad];
-    float M = -INFINITY, Z = 0.f;
-#pragma unroll
-    for (int j = 0; j < kMergeInline; ++j)
-        if (j < n_split) M = fmaxf(M, v[j].x);
-#pragma unroll
-    for (int j = 0; j < kMergeInline; ++j)
-        if (j < n_split) Z += v[j].y * fast_exp2(v[j].x - M);
-    return M + __log2f(Z);
-}
 
 // The accumulator start values of the column-sum pass: Ls[rb][hf][i] = -lse2 / sl2
 // of row rc0 + 32 rb + 8 (i / 4) + 4 hf + i % 4, the row that element i of an
@@ -156,9 +138,9 @@ __device__ __forceinline__ void stage_lse(float (*Ls)[2][16], int nt, int l, int
         const float x = row >= n_rows ? INFINITY
                         : q_lse ? q_lse[((size_t)l * Qn + row / G) * H + g * G + row % G] * kLog2e
                         : n_merge
-                            ? merge_stats_inline((const float2*)lse2 +
-                                                     ((size_t)l * Hkv + g) * n_merge * rows_pad + row,
-                                                 n_merge, rows_pad)
+                            ? merge_stats((const float2*)lse2 +
+                                              ((size_t)l * Hkv + g) * n_merge * rows_pad + row,
+                                          n_merge, rows_pad)
                             : lse2[((size_t)l * Hkv + g) * rows_pad + row];
         Ls[rb][hh][i] = -x / sl2;
     }
@@ -792,7 +774,7 @@ void launch_passes_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, char*
                   "a full-size split is whole rounds of both passes");
     const int kps = stats_split(p);
     const dim3 kgrid((p.T_c + kps - 1) / kps, p.H_kv, p.L);
-    const bool inline_merge = !p.q_lse && w.n_split <= kMergeInline && w.rows_pad <= kMergeInlineRows;
+    const bool inline_merge = !p.q_lse && w.n_split <= kMergeInline && w.rows_pad <= kKregRowBlocks * 32;
     if (!p.q_lse) {
         hipLaunchKernelGGL((score_stats_kreg<D, KNW, KNKB>), kgrid, dim3(KNW * 64), 0, st, q, kc,
                            kv_strides(p), p.T_c, p.n_query, p.H, p.H_kv, G, n_rows, w.rows_pad, kps, w.n_split,

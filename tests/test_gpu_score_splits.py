@@ -32,7 +32,9 @@ def test_score_splits(gpu_lib, L, T, H, H_kv, d, Qn):
         assert_close(a[check].cpu().numpy(), a_ref, w, "scores", rel_gate=1e-2)
 
 
-# rows past the inline merge's limit (2048 + 32), and eight splits within it
-@pytest.mark.parametrize("L,T,H,H_kv,d,Qn", [(1, 3000, 16, 2, 64, 260), (1, 4096, 16, 2, 64, 256), (1, 30000, 6, 2, 128, 30)])
+# 320 rows (one chunk, its statistics merged while staging), 352 (a merge launch), eight
+# splits merged while staging and nine by the launch
+@pytest.mark.parametrize("L,T,H,H_kv,d,Qn", [(1, 3000, 16, 2, 64, 40), (1, 3000, 16, 2, 64, 44),
+                                             (1, 32768, 6, 2, 128, 30), (1, 32769, 6, 2, 128, 30)])
 def test_score_merge_sides(gpu_lib, L, T, H, H_kv, d, Qn):
     test_score_splits(gpu_lib, L, T, H, H_kv, d, Qn)
