@@ -27,7 +27,7 @@ inline KvStrides kv_strides(const relaxkv_problem& p) {
 struct ScoreWorkspace {
     size_t part_off;    // float [L][n_part][T_c]   per-KV-head pooled partial sums
     size_t stats_off;   // float2 [L][H_kv][n_split][rows_pad] (max, sum) per key split, log2
-                        // units (float32: natural, only for more than one split)
+                        // units (float32: per unit, natural, only for more than one split)
     size_t lse_off;     // float [L][H_kv][rows_pad] row log2-sum-exp
     size_t mm_off;      // float2 [L][n_blk] (min, max) of p per finaliser block
     size_t total;

@@ -418,9 +418,9 @@ __global__ void score_merge(const float2* __restrict__ stats, int n_groups, int 
 // heads, d 128, 8.06 -> 0.53 ms; 2 layers of 1024 keys, 4q/2kv heads 44 -> 23 us.
 constexpr int kF32Waves = 8;            // of the column sums
 constexpr int kF32StatsWaves = 16;
-constexpr int kF32Unit = kF32StatsWaves * 32;            // keys per unit of the row statistics
-constexpr int kF32Batch = 8;                             // units between two barriers
-constexpr int kF32Table = 64;                            // most units a workgroup merges itself
+constexpr int kF32Round = kF32StatsWaves * 32;           // keys of a workgroup per round
+constexpr int kF32Units = 64;                            // most units of the row statistics
+constexpr int kF32Batch = 8;                             // units between two merges
 
 template <int D>
 __device__ __forceinline__ void load_row_f32(f32x4 (&dst)[D / 8], const float* p, int hf) {
@@ -438,13 +438,14 @@ __device__ __forceinline__ f32x16 dot_f32(const f32x4 (&a)[D / 8], const f32x4 (
     return s;
 }
 
-// Row statistics over units of 512 keys: a workgroup takes 32 (token, head) rows of a KV
-// head of a layer and `per` consecutive units, one 32-key block per wave and unit (S^T
-// = K Q^T, one row per lane; Q staged in LDS, the next unit's K loaded behind this
-// one's products).  Every kF32Batch units the waves' (max, sum) of each unit are merged
-// in wave order, a wave per unit; the units' pairs are merged in order, by the workgroup
-// if it has them all (and they fit its table), else by score_merge_f32: the same bits
-// however the units are spread over workgroups.
+// Row statistics over units of n_round rounds of 512 keys (one round up to 32768 keys, as
+// many as make 64 units past that): a workgroup takes 32 (token, head) rows of a KV head
+// of a layer and `per` consecutive units, one 32-key block per wave and round (S^T =
+// K Q^T, one row per lane; Q staged in LDS, the next round's K loaded behind this one's
+// products).  Every kF32Batch units the waves' (max, sum) of each unit are merged in wave
+// order, a wave per unit; the units' pairs are merged in order, by the workgroup if it has
+// them all, else by score_merge_f32.  The units depend on T only, so the bits are the same
+// however they are spread over workgroups.
 __device__ __forceinline__ float merge_units_f32(const float2* __restrict__ s, int n, size_t stride) {
     float M = -INFINITY, Z = 0.f;
 #pragma unroll 8                                         // (loads in flight, in-order sum)
@@ -457,32 +458,31 @@ __device__ __forceinline__ float merge_units_f32(const float2* __restrict__ s, i
 template <int D>
 __global__ __launch_bounds__(kF32StatsWaves * 64) void score_stats_f32(
     const float* __restrict__ q, const float* __restrict__ kc, KvStrides ks, int T, int Qn, int H,
-    int Hkv, int G, int n_rows, int rows_pad, int n_unit, int per, float scale,
+    int Hkv, int G, int n_rows, int rows_pad, int n_unit, int n_round, int per, float scale,
     float2* __restrict__ stats, float* __restrict__ lse_nat) {
     __shared__ f32x4 Qs[D / 8][64];
-    __shared__ float2 red[kF32Batch][kF32StatsWaves][32], table[kF32Table][32];
+    __shared__ float2 red[kF32Batch][kF32StatsWaves][32], table[kF32Units][32];
     const int g = blockIdx.y, l = blockIdx.z;
     const int n_split = (n_unit + per - 1) / per;
     const int rb = blockIdx.x / n_split, u0 = (blockIdx.x - rb * n_split) * per;
     const int u1 = min(n_unit, u0 + per);
-    const bool own = n_split == 1 && n_unit <= kF32Table;
+    const bool own = n_split == 1;
     const int tid = threadIdx.x, lane = tid & 63, r32 = lane & 31, hf = lane >> 5;
     const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int row = rb * 32 + r32, rr = min(row, n_rows - 1);
     const size_t lg = (size_t)l * Hkv + g;
     const float* Kg = kc + l * ks.layer + g * ks.head;
     f32x4 kf[D / 8];
-    auto load_k = [&](int u) {
-        load_row_f32<D>(kf, Kg + min(u * kF32Unit + w * 32 + r32, T - 1) * ks.token, hf);
-    };
-    load_k(u0);
+    auto load_k = [&](int k0) { load_row_f32<D>(kf, Kg + min(k0 + r32, T - 1) * ks.token, hf); };
+    int k0 = u0 * n_round * kF32Round + w * 32;
+    load_k(k0);
     const float* qrow = q + (((size_t)l * Qn + rr / G) * H + g * G + rr % G) * D;
     for (int j = w; j < D / 8; j += kF32StatsWaves) Qs[j][lane] = *(const f32x4*)(qrow + 8 * j + 4 * hf);
     __syncthreads();
     for (int u = u0; u < u1; ++u) {
         float m = -INFINITY, z = 0.f;
-        const int k0 = u * kF32Unit + w * 32;
-        if (k0 < T) {
+        for (int r = 0; r < n_round; ++r, k0 += kF32Round) {
+            if (k0 >= T) continue;
             f32x16 s = f32x16{};
 #pragma unroll
             for (int j = 0; j < D / 8; ++j) {
@@ -491,18 +491,21 @@ __global__ __launch_bounds__(kF32StatsWaves * 64) void score_stats_f32(
                 for (int i = 0; i < 4; ++i)
                     s = __builtin_amdgcn_mfma_f32_32x32x2f32(kf[j][i], qj[i], s, 0, 0, 0);
             }
-            if (u + 1 < u1) load_k(u + 1);
+            if (r + 1 < n_round || u + 1 < u1) load_k(k0 + kF32Round);
             const int ex = T - 1 - k0 - 4 * hf;          // last key of the block
+            float mx = m;
 #pragma unroll
             for (int v = 0; v < 16; ++v) {
                 s[v] = 8 * (v >> 2) + (v & 3) > ex ? -INFINITY : s[v] * scale;
-                m = fmaxf(m, s[v]);
+                mx = fmaxf(mx, s[v]);
             }
-            m = fmaxf(m, __shfl_xor(m, 32, 64));         // (the row's other half-wave)
+            mx = fmaxf(mx, __shfl_xor(mx, 32, 64));      // (the row's other half-wave)
+            z *= expf(m - mx);
+            m = mx;
 #pragma unroll
             for (int v = 0; v < 16; ++v) z += expf(s[v] - m);
-            z += __shfl_xor(z, 32, 64);
         }
+        z += __shfl_xor(z, 32, 64);
         const int x = (u - u0) % kF32Batch;
         if (hf == 0) red[x][w][r32] = make_float2(m, z);
         if (x + 1 < kF32Batch && u + 1 < u1) continue;
@@ -800,17 +803,25 @@ hipError_t launch_score_bf16(const relaxkv_problem& p, const ScoreWorkspace& w, 
     return hipGetLastError();
 }
 
-// Units per workgroup of the float32 statistics: as many splits as give each CU at most
+// The float32 statistics' rounds per unit, units, and units per workgroup: as many splits as give each CU at most
 // one workgroup, since a workgroup's units are a serial chain.  Self-contained scores
 // in us, one workgroup per row and VALU / one per 32 rows and all keys / split: one
 // layer of 30000 keys and 64 rows 286 / 422 / 34, of 8000 and 24 rows 185 / 189 / 40, 2
 // of 2000 and 2 rows 29 / 37 / 21, 2 of 1024 and 32 rows 43 / 27 / 20, 4 of 3000 and
 // 2048 rows (256 workgroups: not split) 4997 / 186 / 184.
-int f32_stats_units(const relaxkv_problem& p) {
+struct F32Units {
+    int n_round, n_unit, per;
+};
+F32Units f32_units(const relaxkv_problem& p) {
     constexpr long kCUs = 256;
+    const int rounds = (p.T_c + kF32Round - 1) / kF32Round;
+    F32Units u;
+    u.n_round = (rounds + kF32Units - 1) / kF32Units;
+    u.n_unit = (rounds + u.n_round - 1) / u.n_round;
     const long wg = (long)(round_up32(p.n_query * (p.H / p.H_kv)) / 32) * p.H_kv * p.L;
-    const long n = (p.T_c + kF32Unit - 1) / kF32Unit, split = wg >= kCUs ? 1 : kCUs / wg;
-    return (int)((n + split - 1) / split);
+    const int split = wg >= kCUs ? 1 : (int)(kCUs / wg);
+    u.per = (u.n_unit + split - 1) / split;
+    return u;
 }
 
 template <int D>
@@ -823,14 +834,15 @@ hipError_t launch_score_f32(const relaxkv_problem& p, const ScoreWorkspace& w, c
     float* lse = (float*)(ws + w.lse_off);
     if (!p.q_lse) {
         float2* stats = (float2*)(ws + w.stats_off);
-        const int per = f32_stats_units(p), n_split = (w.n_split + per - 1) / per;
-        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32 * n_split, p.H_kv, p.L),
+        const F32Units u = f32_units(p);
+        hipLaunchKernelGGL(score_stats_f32<D>, dim3(w.rows_pad / 32 * w.n_split, p.H_kv, p.L),
                            dim3(kF32StatsWaves * 64), 0, st, q, kc, kv_strides(p), p.T_c, p.n_query,
-                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, w.n_split, per, scale, stats, lse);
+                           p.H, p.H_kv, G, p.n_query * G, w.rows_pad, u.n_unit, u.n_round, u.per, scale,
+                           stats, lse);
         const long n = (long)p.L * p.H_kv * w.rows_pad;
-        if (n_split > 1 || w.n_split > kF32Table)
+        if (w.n_split > 1)
             hipLaunchKernelGGL(score_merge_f32, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, st,
-                               (const float2*)stats, p.L * p.H_kv, w.n_split, w.rows_pad, p.n_query * G,
+                               (const float2*)stats, p.L * p.H_kv, u.n_unit, w.rows_pad, p.n_query * G,
                                lse);
     }
     hipLaunchKernelGGL(score_colsum_f32<D>, dim3((p.T_c + 31) / 32, p.L), dim3(kF32Waves * 64), 0, st,
@@ -848,13 +860,16 @@ ScoreWorkspace score_workspace_layout(const relaxkv_problem& p) {
     const int G = p.H / p.H_kv;
     const bool bf = p.dtype == RELAXKV_DTYPE_BF16;
     w.rows_pad = round_up32(p.n_query * G);
-    const int kps = bf ? stats_split(p) : kF32Unit;
-    w.n_split = (p.T_c + kps - 1) / kps;
+    const F32Units u = f32_units(p);
+    const int kps = stats_split(p);
+    w.n_split = bf ? (p.T_c + kps - 1) / kps : (u.n_unit + u.per - 1) / u.per;
     w.n_part = bf ? p.H_kv : 1;
     w.part_off = 0;
     size_t off = al((size_t)p.L * w.n_part * p.T_c * sizeof(float));
     w.stats_off = off;
-    if (bf || w.n_split > 1) off += al((size_t)p.L * p.H_kv * w.n_split * w.rows_pad * sizeof(float2));
+    // (float32: a pair per unit, only where a merge launch reads them: below 256 row blocks)
+    const int n_pair = bf ? w.n_split : w.n_split > 1 ? u.n_unit : 0;
+    off += al((size_t)p.L * p.H_kv * n_pair * w.rows_pad * sizeof(float2));
     w.lse_off = off;
     off += al((size_t)p.L * p.H_kv * w.rows_pad * sizeof(float));
     w.n_blk = (p.T_c + kFinKeys - 1) / kFinKeys;

@@ -64,10 +64,11 @@ def test_f32_rows(gpu_lib, T, H, H_kv, Qn, n, d):
     assert_close(lse.cpu().numpy(), lse_ref, w, "query lse")
 
 
-# The row statistics' 512-key units: 4 (the last of one key), 3 and 18 of them, each in
-# a workgroup of its own or several in one (past 8, several batches), merged by a launch.
+# The row statistics' units: 4 (the last of one key), 3 and 18 of 512 keys, each in a
+# workgroup of its own or several in one (past 8, several batches), and 40 of 1024 keys.
 @pytest.mark.parametrize("d", [64, 128])
-@pytest.mark.parametrize("L,T,H,H_kv,Qn", [(1, 1537, 2, 2, 1), (2, 1500, 6, 2, 30), (2, 9000, 8, 4, 130)])
+@pytest.mark.parametrize("L,T,H,H_kv,Qn", [(1, 1537, 2, 2, 1), (2, 1500, 6, 2, 30), (2, 9000, 8, 4, 130),
+                                           (1, 40001, 2, 1, 2)])
 def test_f32_score_units(gpu_lib, L, T, H, H_kv, Qn, d):
     w = synth.shrink(W, L=L, T_c=T, H=H, H_kv=H_kv, Qn=Qn, d=d)
     case = Case(w)
@@ -90,8 +91,8 @@ def test_f32_layer_scores_do_not_depend_on_the_other_layers(gpu_lib, T):
     assert torch.equal(scores(64)[:1], scores(1)) and torch.equal(scores(64)[:7], scores(7))
 
 
-def test_f32_score_more_units_than_a_workgroup_merges(gpu_lib):
-    """65 units, all in the one workgroup of each of 256 KV heads."""
+def test_f32_score_all_units_in_one_workgroup(gpu_lib):
+    """33 units of 1024 keys (the last of 3), all in the one workgroup of each of 256 KV heads."""
     T, H, d = 64 * 512 + 3, 256, 64
     g = torch.Generator(device="cuda").manual_seed(5)
     q = torch.randn(1, 1, H, d, device="cuda", generator=g)
