@@ -36,6 +36,9 @@
  *   Element types: int32 for indices and counts, int64 for edge counts,
  *   float32 for scores and log-sum-exp values, and `dtype` (bfloat16 or
  *   float32) for Q/K/V and attention outputs.
+ * - An Inf or NaN in a key or value reaches the outputs of the rows that see its
+ *   position; in the bf16 attention calls one in a value may also reach rows of the
+ *   call that do not (masked keys are multiplied by 0 there).
  * - Layers are 0-based; positions are context positions 0 .. T_c-1 (the
  *   query tokens are never targets or context).
  * - The library keeps no host state between calls (besides the per-device
