@@ -33,7 +33,8 @@ def check(case, U, h, cidx, R, R_u):
         assert edges[L + l] == int((np.asarray(R[l]) + 1).sum())
 
 
-@pytest.mark.parametrize("L,T,ratio", [(2, (1 << 20) + 1, 0.9), (1, (1 << 20) + 16385, 0.3), (2, 1 << 22, 1.0)])
+@pytest.mark.parametrize("L,T,ratio", [(2, (1 << 20) + 1, 0.9), (1, (1 << 20) + 16385, 0.3), (2, 1 << 22, 1.0),
+                                       (65, (1 << 19) + 1, 0.3)])
 def test_largest_set_blocks(gpu_lib, L, T, ratio):
     case = Lists(L, T, ratio)
     rng = np.random.default_rng(T)
