@@ -66,10 +66,12 @@ __device__ __forceinline__ int lower_bound16(const int32_t* __restrict__ a, int 
 // atomics) and then over the layers, instead of once per layer.  One workgroup per
 // block goes through all layers, so with many of them and few blocks these chains
 // were longer than the four launches before (16.5 us at 128 layers of 64 positions, 54
-// at 1024 of 1024).  Both launches in us, without / with it: 8 layers of 1531 positions
-// 9.4 / 11.1, 40 of 32768 18.1 / 18.6, 64 of 1024 12.8 / 14.8, 128 of 1024 19.4 / 16.2,
-// 512 of 4096 78 / 50, 1024 of 64 69 / 23, 1024 of 1024 106 / 48.
-constexpr int kFewLayers = 64;
+// at 1024 of 1024).  Both launches in us, without / with it: 40 layers of 32768 positions
+// 18.1 / 18.6, 80 of 16384 23.8 / 25.5, 96 of 4096 20.2 / 20.7, 128 of 1024 19.3 / 16.1,
+// 256 of 16384 60 / 46, 1024 of 64 69 / 22, 1024 of 1024 107 / 48; a global list, which
+// has no counts per layer: 80 of 65536 32.7 / 37.7, 128 of 16384 22.7 / 25.3, 256 of 1024
+// 18.5 / 18.0, of 16384 36.8 / 35.5, 1024 of 64 34 / 22, of 1024 47.9 / 44.2.
+constexpr int kFewLayers = 96, kFewLayersGlobal = 192;
 static_assert(RELAXKV_MAX_LAYERS <= kSetThreads, "one layer per thread");
 
 // lower_bound16 of N lists at once.
@@ -677,7 +679,7 @@ void launch_blocks(const relaxkv_problem& p, const relaxkv_sets& s, int pb, cons
                            s.anchors, p.L, s.k, p.T_c, pb, P, n_P, s.h, sc, s.tiles,
                            (int)attn_tile_words(p));
     };
-    if (p.L > kFewLayers) go(sets_blocks<GT, true>);
+    if (p.L > (GT ? kFewLayersGlobal : kFewLayers)) go(sets_blocks<GT, true>);
     else go(sets_blocks<GT, false>);
 }
 

@@ -263,6 +263,15 @@ class Request:
         self._scores_shape = (L, T_c)
         self._q_shape, self._kq_shape, self._lse_shape = (Qn, H, d), (Qn, H_kv, d), (Qn, H)
 
+    @property
+    def p(self):
+        """The descriptor; its reference, which every call passes, changes with it."""
+        return self._p
+
+    @p.setter
+    def p(self, problem):
+        self._p, self._ref = problem, ctypes.byref(problem)
+
     # ---- sizes and buffers (device memory comes from torch)
     def workspace_bytes(self):
         return load().relaxkv_score_workspace_bytes(ctypes.byref(self.p))
@@ -315,18 +324,18 @@ class Request:
     def score(self, ws, scores, stream=None):
         self._ws(ws)
         self._scores(scores)
-        _check(self._lib.relaxkv_score(ctypes.byref(self.p), _ptr(ws), _nbytes(ws), _ptr(scores),
+        _check(self._lib.relaxkv_score(self._ref, _ptr(ws), _nbytes(ws), _ptr(scores),
                                     _stream(stream)), "relaxkv_score")
 
     def select(self, scores, sets, stream=None):
         self._scores(scores)
         self._sets(sets)
-        _check(self._lib.relaxkv_select(ctypes.byref(self.p), _ptr(scores), ctypes.byref(sets.s),
+        _check(self._lib.relaxkv_select(self._ref, _ptr(scores), ctypes.byref(sets.s),
                                      _stream(stream)), "relaxkv_select")
 
     def build_sets(self, sets, stream=None):
         self._sets(sets)
-        _check(self._lib.relaxkv_build_sets(ctypes.byref(self.p), ctypes.byref(sets.s),
+        _check(self._lib.relaxkv_build_sets(self._ref, ctypes.byref(sets.s),
                                          _stream(stream)), "relaxkv_build_sets")
 
     def build_sets_context(self, scores, construction, sets, stream=None):
@@ -334,7 +343,7 @@ class Request:
         (CONTEXT_SETS_UNION / _GLOBAL / _LAYERWISE); scores [L][T_c] f32."""
         self._scores(scores)
         self._sets(sets)
-        _check(self._lib.relaxkv_build_sets_context(ctypes.byref(self.p), _ptr(scores),
+        _check(self._lib.relaxkv_build_sets_context(self._ref, _ptr(scores),
                                                  int(construction), ctypes.byref(sets.s),
                                                  _stream(stream)), "relaxkv_build_sets_context")
 
@@ -346,7 +355,7 @@ class Request:
         self._want(g, "g", torch.float32, (self.T_c,))
         self._want(targets, "targets", torch.int32, (self.T_c,))
         self._want(n_targets, "n_targets", torch.int32, (1,))
-        _check(self._lib.relaxkv_select_global(ctypes.byref(self.p), _ptr(scores),
+        _check(self._lib.relaxkv_select_global(self._ref, _ptr(scores),
                                             float(target_ratio), ctypes.byref(sets.s), _ptr(g),
                                             _ptr(targets), _ptr(n_targets), _stream(stream)),
                "relaxkv_select_global")
@@ -357,7 +366,7 @@ class Request:
         self._sets(sets)
         self._want(targets, "targets", torch.int32, (self.T_c,))
         self._want(n_targets, "n_targets", torch.int32, (1,))
-        _check(self._lib.relaxkv_build_sets_global(ctypes.byref(self.p), ctypes.byref(sets.s),
+        _check(self._lib.relaxkv_build_sets_global(self._ref, ctypes.byref(sets.s),
                                                 _ptr(targets), _ptr(n_targets), _stream(stream)),
                "relaxkv_build_sets_global")
 
@@ -374,7 +383,7 @@ class Request:
         self._want(out, "out", self.dtype, (n, self.H, self.d))
         if lse_out is not None:
             self._want(lse_out, "lse_out", torch.float32, (n, self.H))
-        _check(self._lib.relaxkv_sparse_attn(ctypes.byref(self.p), ctypes.byref(sets.s), int(layer),
+        _check(self._lib.relaxkv_sparse_attn(self._ref, ctypes.byref(sets.s), int(layer),
                                           _ptr(q_new), _ptr(k_new), _ptr(v_new), int(n),
                                           _ptr(out), _ptr(lse_out), int(context_mode),
                                           _stream(stream)),
@@ -388,7 +397,7 @@ class Request:
         self._want(k_new, "k_new", self.dtype, (n, self.H_kv, self.d))
         self._want(v_new, "v_new", self.dtype, (n, self.H_kv, self.d))
         self._caches(k_cache, v_cache)
-        _check(self._lib.relaxkv_update_cache(ctypes.byref(self.p), ctypes.byref(sets.s), int(layer),
+        _check(self._lib.relaxkv_update_cache(self._ref, ctypes.byref(sets.s), int(layer),
                                            _ptr(k_new), _ptr(v_new), int(n), _ptr(k_cache),
                                            _ptr(v_cache), _stream(stream)),
                "relaxkv_update_cache")
@@ -415,7 +424,7 @@ class Request:
             self._want(lse_out, "lse_out", torch.float32, self._lse_shape)
         if ws is not None:
             self._ws(ws)
-        _check(self._lib.relaxkv_query_attn(ctypes.byref(self.p), int(layer), _ptr(k_cache),
+        _check(self._lib.relaxkv_query_attn(self._ref, int(layer), _ptr(k_cache),
                                          _ptr(v_cache), _ptr(k_q), _ptr(v_q), _ptr(out),
                                          _ptr(lse_out), _ptr(ws), 0 if ws is None else _nbytes(ws),
                                          _stream(stream)), "relaxkv_query_attn")
@@ -431,7 +440,7 @@ class Request:
         self._want(out, "out", self.dtype, self._q_shape)
         if lse_out is not None:
             self._want(lse_out, "lse_out", torch.float32, self._lse_shape)
-        _check(self._lib.relaxkv_query_attn_noalloc(ctypes.byref(self.p), int(layer), _ptr(k_cache),
+        _check(self._lib.relaxkv_query_attn_noalloc(self._ref, int(layer), _ptr(k_cache),
                                                  _ptr(v_cache), _ptr(k_q), _ptr(v_q), _ptr(out),
                                                  _ptr(lse_out), _stream(stream)),
                "relaxkv_query_attn_noalloc")

@@ -57,7 +57,7 @@ def test_set_blocks(gpu_lib, L, T):
 
 # around the layer counts where the blocks are counted by h and several layers are
 # searched at a time
-@pytest.mark.parametrize("L,T", [(64, 300), (65, 256), (65, 16385), (200, 2000), (321, 5000)])
+@pytest.mark.parametrize("L,T", [(96, 300), (97, 256), (97, 16385), (192, 700), (193, 2000), (321, 5000)])
 def test_set_blocks_many_layers(gpu_lib, L, T):
     test_set_blocks(gpu_lib, L, T)
 

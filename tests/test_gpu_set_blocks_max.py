@@ -34,7 +34,7 @@ def check(case, U, h, cidx, R, R_u):
 
 
 @pytest.mark.parametrize("L,T,ratio", [(2, (1 << 20) + 1, 0.9), (1, (1 << 20) + 16385, 0.3), (2, 1 << 22, 1.0),
-                                       (65, (1 << 19) + 1, 0.3)])
+                                       (97, (1 << 19) + 1, 0.3), (193, (1 << 19) + 1, 0.3)])
 def test_largest_set_blocks(gpu_lib, L, T, ratio):
     case = Lists(L, T, ratio)
     rng = np.random.default_rng(T)
